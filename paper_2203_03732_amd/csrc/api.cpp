@@ -677,6 +677,8 @@ struct prot_batch {
     int32_t kcap = 0;
     int32_t *err = nullptr;
     unsigned int *queue = nullptr;
+    uint32_t *lists = nullptr;       // candidate lists of the LDS engine
+    int64_t phase_bound = 0;         // its watchdog (BatchArgs)
     prot_instance_stats *stats_tmp = nullptr;
     float *mfma_buf = nullptr;
     int64_t mfma_cap = 0;
@@ -709,10 +711,11 @@ int upload(prot_ctx *c, T **dst, const std::vector<T> &src)
     return PROT_OK;
 }
 
-// Chooses between the LDS-resident batched kernel (instances up to n = 1024)
-// and teams of phase-loop workgroups (larger instances), and for teams builds
-// every instance's loop arguments and workspace. PROT_BATCH_TEAM=<w> forces
-// w workgroups per instance (0: never use teams).
+// Chooses between the LDS-resident batched kernel (one workgroup per
+// instance) and teams of phase-loop workgroups, and for teams builds every
+// instance's loop arguments and workspace. PROT_BATCH_TEAM=<w> forces w
+// workgroups per instance (0: never use teams).
+constexpr int32_t kTeamsMaxBatch = 32;  // 256 CUs / teams of 8
 int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
                 const std::vector<int32_t> &ldk, const std::vector<int64_t> &pt_off,
                 const std::vector<int64_t> &k_off, const prot_batch_config *cfg)
@@ -722,7 +725,21 @@ int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
     else if (cfg && cfg->engine == PROT_BATCH_ENGINE_TEAMS) forced = cfg->team > 0 ? cfg->team : -2;
     else if (const char *v = std::getenv("PROT_BATCH_TEAM")) forced = std::atoi(v);
     const bool must = cfg && cfg->engine == PROT_BATCH_ENGINE_TEAMS;
+    // Automatic choice: one workgroup per instance, except for few large
+    // instances (each can have 8 workgroups) where the candidate lists do not
+    // pay: in two or three dimensions a row has more admissible columns than
+    // a list holds and every scan reads the matrix (n = 2048, d = 2: eps =
+    // 0.05 0.19 ms by teams, 0.25 by one workgroup; 8 instances, eps = 0.01,
+    // shifted clouds 14.1 against 14.8 ms), and at large eps a solve has too
+    // few phases to earn back the first lists (n = 1100, d = 16, eps = 0.1, 2
+    // phases: 0.17 against 0.37 ms; n = 1200, d = 4, eps = 0.05: 0.13 against
+    // 0.16). Elsewhere one workgroup wins (ms, teams / one workgroup: 1 x
+    // 2048, d = 64, eps = 0.01 6.2 / 3.0; 32 x 2048 7.9 / 4.3; 4 x 2048, d =
+    // 8, eps = 0.02 2.1 / 2.0; 300 x 2048, d = 2 35.7 / 15.6).
     if (forced == 0 || (forced == -1 && bp->n_max <= 1024)) return PROT_OK;
+    if (forced == -1) bp->phase_bound = bp->opts.phase_bound;
+    if (forced == -1 && ((bp->d > 3 && bp->eps < 0.04) || bp->batch > kTeamsMaxBatch))
+        return PROT_OK;
     const int32_t n_pad_max = (int32_t)round_up(bp->n_max, 8);
     int gm = 0;
     hipError_t e = prot::loop_grid_multi(n_pad_max, c->wgs_per_cu, &gm);
@@ -872,6 +889,8 @@ int batch_enqueue(prot_batch *bp, hipStream_t s, const float *X, const float *Y,
     a.y_b = y_b;
     a.stats = reinterpret_cast<prot::InstanceStats *>(stats ? stats : bp->stats_tmp);
     a.queue = bp->queue;
+    a.lists = bp->lists;
+    a.phase_bound = bp->phase_bound;
     a.rtime = c->rtime;
     a.err = bp->err;
     HIP_TRY(c, prot::launch_batch_solve(a, bp->n_max, bp->grid, s));
@@ -1855,6 +1874,8 @@ int prot_batch_create_config(prot_ctx *c, int32_t batch, const int64_t *n_host, 
         bp->mfma = j.mfma;
     }
     if (!rc && batch > 0) rc = setup_teams(c, bp, n_arr, ldk, pt_off, k_off, cfg);
+    if (!rc && batch > 0 && bp->team == 0)
+        rc = dev_alloc(c, &bp->lists, (size_t)pts * prot::kBatchListCap);
     if (rc) {
         prot_batch_destroy(bp);
         return rc;
@@ -1880,6 +1901,7 @@ int prot_batch_destroy(prot_batch *bp)
     (void)hipFree(bp->th);
     (void)hipFree(bp->err);
     (void)hipFree(bp->queue);
+    (void)hipFree(bp->lists);
     (void)hipFree(bp->stats_tmp);
     (void)hipFree(bp->mfma_buf);
     (void)hipFree(bp->loops);

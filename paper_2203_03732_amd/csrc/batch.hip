@@ -7,11 +7,31 @@
 // instance alone: the column keys, the duals, the free and taken lists and
 // the active rows of a round all live in LDS, the round barrier is
 // __syncthreads, and only the rounded-cost matrix (built beforehand by the
-// batched cost kernels) is read from memory. A round scans its active rows
-// with lane groups whose width follows the number of active rows: 4 lanes
-// per row when most rows are active, 64 when a few rows scan long.
+// batched cost kernels) and short lists derived from it are read from memory.
 // The kernel does not need co-resident workgroups, so it can be captured in
 // a HIP graph and replayed.
+//
+// Candidate lists. A free row looks for the first column with
+// v = k + t(a) = y(b) - 1 =: need. Its v never fall (t only grows) and need
+// never falls (y(b) only grows), so a list of all columns with v < V, taken
+// at any time, holds every column the row can find while need < V. Each row
+// keeps such a list of at most kListCap entries (column, k) with its V, and
+// minv, a bound below which it can find nothing: most rows of a phase are
+// settled by minv alone (LDS) or by one 128-byte list, read by 8 lanes,
+// instead of their 2n bytes of the matrix. A row whose need has passed V
+// reads its whole row once (one wave, every chunk in flight), which finds its
+// column and writes the next list, with V as high as kListCap allows. A row
+// with more than kListCap columns at v = need gets no list and is read whole
+// whenever it is scanned.
+//
+// Bound: at first instruction issue (every row is read whole once and its list
+// made: ~2.8 us a row of 2,048 and wave with 16 waves a CU), later latency: a
+// phase of list rows alone takes ~2 us (filter, scan and check, each ended by
+// a workgroup barrier), one with whole rows ~3 us more. Whole batched calls,
+// against keys compared per column and every scan reading the matrix: 512
+// instances of n in [64, 1024], d = 16, eps = 0.05 1.63 -> 1.12 ms; loss and
+// gradient of 64 x 2048, d = 64, eps = 0.01 10.8 -> 5.6 ms (there against
+// teams of 4 workgroups an instance).
 #include "cost_common.h"
 #include "device_common.h"
 #include "internal.h"
@@ -19,212 +39,284 @@
 namespace prot {
 namespace {
 
-constexpr int kBatchThreads = 512;
+constexpr int kListCap = kBatchListCap;  // entries of a row's candidate list
+constexpr int kListLanes = kListCap / 4; // lanes that read one list (16 bytes each)
+constexpr uint32_t kListFill = 0x7FFF0000u;  // column 0 with a k that never matches
+constexpr uint16_t kNone16 = 0xFFFF;
+constexpr int32_t kBatchWideMax = 256;
+// A column's key: the round above the proposing row in reverse order, so that
+// the larger key wins and within a round the smaller row. A key of an earlier
+// round never wins, so keys are not cleared between rounds; before the round
+// field runs out they are (at a phase start).
+constexpr int kKeyRowBits = 11;
+constexpr uint32_t kKeyRowMask = (1u << kKeyRowBits) - 1u;
+constexpr uint32_t kKeyRounds = 1u << (32 - kKeyRowBits);
 
-template <int NMAX>
+__device__ inline uint32_t batch_key(uint32_t r, int b)
+{
+    return (r << kKeyRowBits) | (kKeyRowMask - (uint32_t)b);
+}
+
+template <int NMAX, int NT>
 struct BatchShared {
-    unsigned long long key[NMAX];  // (round << 32) | ~b of the column's current mate
-    int32_t yb[NMAX];              // y(b)
-    int32_t F[2][NMAX];            // free rows: this phase / next phase
-    int32_t ab[2][NMAX];           // active rows of this round / the next
-    int32_t ap[2][NMAX];           // their scan positions
-    int32_t at[NMAX];              // column proposed to this round (-1: exhausted)
-    int32_t L[NMAX];               // columns taken this phase
-    uint16_t t[NMAX];              // -y(a)
-    uint16_t skip[NMAX];           // phases row b is known to find nothing in
-    long long red_k[kBatchThreads];
-    double red_c[kBatchThreads];
-    uint32_t nF[2], nact[2], nL, P, D;
+    alignas(16) uint32_t key[NMAX];
+    alignas(16) uint16_t t[NMAX];  // -y(a)
+    uint16_t mate[NMAX];       // row matched to the column (kNone16: none)
+    uint16_t y[NMAX];          // y(b)
+    uint16_t minv[NMAX];       // no column of row b has k + t below this
+    uint16_t V[NMAX];          // row b's list holds every column with k + t < V (0: no list)
+    uint16_t F[2][NMAX];       // free rows: this phase / next phase
+    // active rows of this round / the next: rows with a list from the front,
+    // rows without one from the back; their scan positions
+    uint16_t ab[2][NMAX];
+    uint16_t ap[2][NMAX];
+    // what a row found this round: a column, or nothing (kNone16) and the
+    // smallest k + t it has
+    uint16_t pa[NMAX];
+    uint16_t pm[NMAX];
+    alignas(16) uint32_t stage[NT / 64][kListCap];  // a wave's list on its way to memory
+    uint32_t wcnt[16];
+    long long red_k[16];
+    double red_c[16];
+    unsigned long long red_s[16];
+    uint32_t nF[2], nl[2], nd[2], prop[2];
     int32_t job;
-    unsigned long long scanned;
 };
 
-// First admissible column not taken before round r, scanning row b from
-// position pos with a group of GS lanes (all lanes of the group get the
-// result). Keys and duals are in LDS.
-// When the row is exhausted, *slack_out is the smallest k + t - need over the
-// columns scanned if none of them was admissible, else 0.
-template <int GS>
-__device__ Hit group_scan(const int16_t *__restrict__ row, const uint16_t *t,
-                          const unsigned long long *key, int n, int origin, int pos, int need,
-                          uint32_t r0, uint32_t r, int gl, int gbase, int *slack_out)
+// Workgroup barrier for LDS only: stores to global memory may still be in
+// flight (__syncthreads waits for them).
+__device__ inline void barrier_lds()
 {
-    int mn = 0x7FFFFFFF;  // smallest k + t seen by this lane
-    bool any_adm = false; // some scanned column was admissible (taken or not)
-    constexpr int CH = GS * 8;
-    constexpr int U = GS >= 16 ? 4 : 8;
-    constexpr unsigned long long GM = GS == 64 ? ~0ull : ((1ull << GS) - 1ull);
-    int lo[2], hi[2];
-    const int c0 = origin + pos;
-    if (c0 < n) {
-        lo[0] = c0; hi[0] = n; lo[1] = 0; hi[1] = origin;
-    } else {
-        lo[0] = c0 - n; hi[0] = origin; lo[1] = 0; hi[1] = 0;
-    }
-    for (int sg = 0; sg < 2; ++sg) {
-        const int slo = lo[sg], shi = hi[sg];
-        if (slo >= shi) continue;
-        int base = slo & ~7;
-        int depth = 1;  // one chunk first: early rows usually hit in it
-        while (base < shi) {
-            uint4 kv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int col0 = base + u * CH + gl * 8;
-                kv[u] = make_uint4(0u, 0u, 0u, 0u);
-                if (u < depth && col0 < shi) kv[u] = *reinterpret_cast<const uint4 *>(row + col0);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u >= depth) break;
-                const int col0 = base + u * CH + gl * 8;
-                uint32_t cand = 0;
-                if (col0 < shi) {
-                    const uint4 tv = *reinterpret_cast<const uint4 *>(t + col0);
-                    const uint32_t rm = range_mask(col0, slo, shi);
-                    cand = match_mask(kv[u], tv, need) & rm;
-                    mn = min(mn, min_sum_masked(kv[u], tv, rm));
-                }
-                any_adm |= cand != 0u;
-                uint32_t hit = 0;
-                for (uint32_t c = cand; c; c &= c - 1) {
-                    const int e = __builtin_ctz(c);
-                    const uint32_t kr = (uint32_t)(key[col0 + e] >> 32);
-                    if (!(kr >= r0 && kr < r)) hit |= 1u << e;
-                }
-                const unsigned long long bal = (__ballot(hit != 0u) >> gbase) & GM;
-                if (bal) {
-                    const int L = gbase + __builtin_ctzll(bal);
-                    const uint32_t h = (uint32_t)__shfl((int)hit, L);
-                    const int a = __shfl(col0, L) + __builtin_ctz(h);
-                    return Hit{a >= origin ? a - origin : a - origin + n, a};
-                }
-            }
-            base += depth * CH;
-            depth = U;
-        }
-    }
-#pragma unroll
-    for (int off = GS / 2; off > 0; off >>= 1) mn = min(mn, __shfl_xor(mn, off));
-    const bool adm = ((__ballot(any_adm) >> gbase) & GM) != 0ull;
-    *slack_out = adm ? 0 : mn - need;
-    return Hit{-1, -1};
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// One proposal round over the active rows with groups of GS lanes.
-template <int GS, int NMAX>
-__device__ void round_pass(BatchShared<NMAX> &S, const int16_t *k, int64_t ldk, int n,
-                           int origin_mode, uint32_t r0, uint32_t r, int ac, int nx)
+// Index for this lane's entry of a list with the given counter (every lane
+// of the wave calls; one atomic per wave).
+__device__ inline uint32_t wave_push(uint32_t *counter, bool want)
 {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int gl = lane & (GS - 1);
-    const int gbase = lane - gl;
-    const int g = tid / GS, ngroups = kBatchThreads / GS;
-    const uint32_t nact = S.nact[ac];
-    unsigned long long scanned = 0;
-    for (uint32_t i = g; i < nact; i += ngroups) {
-        const int b = S.ab[ac][i];
-        const int pos = S.ap[ac][i];
-        const int yb = S.yb[b];
-        const int origin = origin_mode == 0 ? b : 0;
-        Hit h{-1, -1};
-        int slack = 0;
-        const int skip = S.skip[b];
-        if (skip == 0)
-            h = group_scan<GS>(k + (int64_t)b * ldk, S.t, S.key, n, origin, pos, yb - 1, r0, r,
-                               gl, gbase, &slack);
-        if (gl != 0) continue;
-        if (skip > 0) {
-            // Exact fast-forward: an earlier full scan of this row found no
-            // admissible column, every slack k + t - (y(b) - 1) was >= skip + 1
-            // then, and since y(b) has grown by one per phase while t only
-            // grows, no column can be admissible yet; the scan would exhaust.
-            S.skip[b] = (uint16_t)(skip - 1);
-        } else if (pos == 0 && slack >= 2) {
-            // the row's first scan of this phase covered every column
-            S.skip[b] = (uint16_t)min(slack - 1, 65535);
+    const unsigned long long bal = __ballot(want);
+    uint32_t at = 0;
+    if (bal != 0ull && (threadIdx.x & 63) == 0) at = atomicAdd(counter, (uint32_t)__popcll(bal));
+    return __builtin_amdgcn_readfirstlane(at) + lanes_below(bal);
+}
+
+// Two 16-bit values at a time.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ inline u16x2 as_pair(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
+__device__ inline uint32_t as_word(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
+
+// In each half: 1 if its value exceeds D's, else 0 (a saturating subtraction
+// and a minimum; written out because the compiler takes the pair apart into
+// two compares and two selects). one: 1 in both halves.
+__device__ inline uint32_t pairs_above(uint32_t v, uint32_t D, uint32_t one)
+{
+    uint32_t r;
+    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(r) : "v"(v), "v"(D));
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(r), "v"(one));
+    return r;
+}
+// Bit e set iff element e of four pairs is at most D, from the OR of
+// pairs_above(word w) << 2w.
+__device__ inline uint32_t low_bits(uint32_t x) { return ~(x | (x >> 15)) & 0xFFu; }
+
+// A whole row held by one wave: chunk c is columns 512 c + 8 lane .. + 7.
+template <int NC>
+struct RowRegs {
+    uint4 c[NC];
+};
+template <int NC>
+__device__ inline RowRegs<NC> load_row(const int16_t *__restrict__ row, int n, int lane)
+{
+    RowRegs<NC> r;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int col0 = c * 512 + lane * 8;
+        r.c[c] = make_uint4(0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu);
+        if (col0 < n) r.c[c] = *reinterpret_cast<const uint4 *>(row + col0);
+    }
+    return r;
+}
+
+// d[i] for a lane's own index i: a tree of bitwise selects (registers cannot
+// be indexed by a lane's value, and a select written with ?: is turned back
+// into an array in memory).
+template <int N>
+struct SelectWord {
+    static __device__ inline uint32_t get(const uint32_t (&d)[N], uint32_t i)
+    {
+        const uint32_t m = 0u - (i & 1u);
+        uint32_t h[N / 2];
+#pragma unroll
+        for (int e = 0; e < N / 2; ++e) h[e] = (d[2 * e] & ~m) | (d[2 * e + 1] & m);
+        return SelectWord<N / 2>::get(h, i >> 1);
+    }
+};
+template <>
+struct SelectWord<1> {
+    static __device__ inline uint32_t get(const uint32_t (&d)[1], uint32_t) { return d[0]; }
+};
+
+// First admissible column of a row in scan order from column `origin`, by one
+// wave; every column is compared. The row's bounds and list are renewed:
+// *minv = the smallest k + t if nothing is admissible (a column taken this
+// phase counts with its raised t), and the columns with v < *V go to `stage`
+// (kListCap entries of LDS; *V = 0 if more than that have v = need, then there
+// is no list). V - 1 starts *window above the smallest v and is halved towards it
+// until the list fits, or widened while it holds fewer than kListCap / 4.
+// k: the row; S_t: the duals in LDS.
+// Bound: instruction issue (about 3 instructions per 2 columns and pass over
+// the row: the sums and their minimum, then one or two list masks).
+template <int NC>
+__device__ Hit direct_row(const RowRegs<NC> &k, const uint16_t *S_t, int n,
+                          int origin, int need, int lane, uint32_t *stage, uint16_t *minv,
+                          uint16_t *V, int *window)
+{
+    const uint32_t one = 0x10001u;
+    const u16x2 need2 = (u16x2)(uint16_t)need;
+    uint32_t d[4 * NC];  // k + t - need
+    u16x2 mn2 = (u16x2)(uint16_t)0xFFFF;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const uint32_t kw[4] = {k.c[c].x, k.c[c].y, k.c[c].z, k.c[c].w};
+        const int col0 = c * 512 + lane * 8;
+        const uint4 t = *reinterpret_cast<const uint4 *>(S_t + (col0 < n ? col0 : 0));
+        const uint32_t tw[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const u16x2 v = as_pair(kw[w]) + as_pair(tw[w]) - need2;
+            d[4 * c + w] = as_word(v);
+            mn2 = __builtin_elementwise_min(mn2, v);
         }
-        if (h.j >= 0) {
-            scanned += (unsigned long long)(h.j - pos + 1);
-            const unsigned long long kn = ((unsigned long long)r << 32) | (uint32_t)~(uint32_t)b;
-            const unsigned long long old = atomicMax(&S.key[h.a], kn);
-            S.at[i] = h.a;
-            S.ap[ac][i] = h.j;
-            atomicAdd(&S.P, 1u);
-            if ((uint32_t)(old >> 32) < r) {
-                // first proposal to a this round: a is in M' whoever wins;
-                // step (II) evicts its old mate, (III a) will lower y(a)
-                atomicAdd(&S.D, 1u);
-                S.L[atomicAdd(&S.nL, 1u)] = h.a;
-                if (old != 0ull) S.F[nx][atomicAdd(&S.nF[nx], 1u)] = (int32_t)~(uint32_t)old;
-            }
+    }
+    const int mn = (int)wave_min_u32(min(as_word(mn2) & 0xFFFFu, as_word(mn2) >> 16));
+    // bit 8c + e: column 512 c + 8 lane + e has v <= need + D
+    auto mask_of = [&](int D) {
+        const uint32_t D2 = (uint32_t)D * 0x10001u;
+        uint32_t W = 0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            uint32_t x = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                x |= pairs_above(d[4 * c + w], D2, one) << (2 * w);
+            W |= low_bits(x) << (8 * c);
+        }
+        return W;
+    };
+    Hit h{-1, -1};
+    *minv = (uint16_t)min(0xFFFF, need + mn);
+    if (mn == 0) {
+        const uint32_t M = mask_of(0);
+        uint32_t G = 0;  // columns from the origin on
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int s = origin - (c * 512 + lane * 8);
+            G |= (s <= 0 ? 0xFFu : s >= 8 ? 0u : (0xFFu << s) & 0xFFu) << (8 * c);
+        }
+        uint32_t j = 0x7FFFFFFFu;
+        if (M != 0u) {
+            const uint32_t A = M & G;
+            const int i = __builtin_ctz(A ? A : M);
+            const int col = (i >> 3) * 512 + lane * 8 + (i & 7);
+            j = (uint32_t)(A ? col - origin : col - origin + n);
+        }
+        h.j = (int)wave_min_u32(j);
+        h.a = origin + h.j < n ? origin + h.j : origin + h.j - n;
+    }
+    // padding has v - need = 0x7FFF - need, above dcap
+    const int dcap = 0x7FFE - need;
+    if (mn > dcap) {  // (nothing within 15 bits: every v is at least minv)
+        *V = 0;
+        return h;
+    }
+    int D = min(mn + *window, dcap);
+    uint32_t W, incl;
+    int cnt;
+    for (bool grown = false;;) {
+        W = mask_of(D);
+        incl = wave_inclusive_sum_u32((uint32_t)__builtin_popcount(W));
+        cnt = __builtin_amdgcn_readlane((int)incl, 63);
+        if (cnt > kListCap) {
+            if (D == mn) break;
+            D = mn + ((D - mn) >> 1);
+            grown = true;  // do not widen again
+        } else if (!grown && cnt < kListCap / 4 && D < dcap) {
+            const int next = min(D + 1 + ((D - mn) >> 1), dcap);
+            if (D - mn > 64) grown = true;
+            D = next;
         } else {
-            // no admissible untaken column: b stays free in M', (III b)
-            scanned += (unsigned long long)(n - pos);
-            S.yb[b] = yb + 1;
-            S.F[nx][atomicAdd(&S.nF[nx], 1u)] = b;
-            S.at[i] = -1;
+            break;
         }
     }
-    if (scanned) atomicAdd(&S.scanned, scanned);
-}
-
-// Writes, in ascending order, the indices i < n with flag(i) into out;
-// returns their number. All threads of the block call it.
-template <int NMAX, class Flag>
-__device__ int ordered_list(BatchShared<NMAX> &S, int n, Flag flag, int32_t *out)
-{
-    const int tid = threadIdx.x;
-    const int per = (n + kBatchThreads - 1) / kBatchThreads;
-    const int lo = min(n, tid * per), hi = min(n, lo + per);
-    int c = 0;
-    for (int i = lo; i < hi; ++i) c += flag(i) ? 1 : 0;
-    long long *cnt = S.red_k;
-    cnt[tid] = c;
-    __syncthreads();
-    for (int off = 1; off < kBatchThreads; off <<= 1) {
-        const long long v = tid >= off ? cnt[tid - off] : 0;
-        __syncthreads();
-        cnt[tid] += v;
-        __syncthreads();
+    *window = D - mn;
+    if (cnt > kListCap) {
+        // too many at the smallest v: an empty list up to it, or none
+        if (mn == 0) {
+            *V = 0;
+            return h;
+        }
+        D = mn - 1;
+        W = 0u;
+        cnt = 0;
+        incl = 0u;
     }
-    int o = (int)cnt[tid] - c;
-    for (int i = lo; i < hi; ++i)
-        if (flag(i)) out[o++] = i;
-    const int total = (int)cnt[kBatchThreads - 1];
-    __syncthreads();
-    return total;
+    *V = (uint16_t)(need + D + 1);
+    uint32_t at = incl - (uint32_t)__builtin_popcount(W);
+    while (W) {
+        const int i = __builtin_ctz(W);
+        W &= W - 1u;
+        const int col = (i >> 3) * 512 + lane * 8 + (i & 7);
+        const uint32_t pair = SelectWord<4 * NC>::get(d, (uint32_t)i >> 1);
+        const uint32_t v = ((i & 1) ? pair >> 16 : pair & 0xFFFFu) + (uint32_t)need;
+        stage[at++] = (uint32_t)col | ((v - S_t[col]) << 16);
+    }
+    if (lane >= cnt && lane < kListCap) stage[lane] = kListFill;
+    return h;
 }
 
-template <int NMAX>
-__device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX> &S, bool timed)
+template <int NMAX, int NT>
+__device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, NT> &S, bool timed)
 {
-    const int tid = threadIdx.x;
+    constexpr int NC = NMAX / 512;
+    constexpr int kWaves = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = A.n_arr[inst];
     const int64_t off = A.pt_off[inst];
     const int16_t *k = A.k + A.k_off[inst];
     const int64_t ldk = A.ldk_arr[inst];
+    uint32_t *lists = A.lists + off * kListCap;
     const int64_t T = (int64_t)floor(A.eps * (double)n + 1e-9);
-    const int64_t bound = (2 * (int64_t)n * ((int64_t)floor(1.0 / A.eps) + 2) - n) / (T + 1);
+    // the watchdog: a cold start needs at most (2n(K + 2) - n) / (T + 1)
+    // phases (Lemma 3.2 with eq. (4)); more means a fault
+    const int64_t bound =
+        A.phase_bound ? A.phase_bound
+                      : (2 * (int64_t)n * ((int64_t)floor(1.0 / A.eps) + 2) - n) / (T + 1);
 
-    // Initial state (Section 2.2): y(b) = 1, y(a) = 0, M empty.
-    for (int i = tid; i < n; i += kBatchThreads) {
-        S.key[i] = 0ull;
-        S.t[i] = 0;
-        S.yb[i] = 1;
-        S.F[0][i] = i;
-        S.skip[i] = 0;
+    // Initial state (Section 2.2): y(b) = 1, y(a) = 0, M empty; no lists
+    // (V = 0) and nothing known (minv = 0 makes every row look).
+    for (int i = tid; i < ((n + 7) & ~7); i += NT) S.t[i] = 0;
+    for (int i = tid; i < n; i += NT) {
+        S.key[i] = 0u;
+        S.mate[i] = kNone16;
+        S.y[i] = 1;
+        S.F[0][i] = (uint16_t)i;
+        S.minv[i] = 0;
+        S.V[i] = 0;
     }
-    for (int i = n + tid; i < ((n + 7) & ~7); i += kBatchThreads) S.t[i] = 0;
     if (tid == 0) {
         S.nF[0] = (uint32_t)n;
-        S.scanned = 0;
+        S.nF[1] = 0;
+        S.nl[0] = S.nl[1] = S.nd[0] = S.nd[1] = S.prop[0] = S.prop[1] = 0;
     }
     int64_t phases = 0, sum_free = 0, rounds = 0, max_rounds = 0;
+    unsigned long long scanned = 0;  // this thread's share
     uint32_t r = 0;
-    int cur = 0;
+    int cur = 0, q = 0;
     int status = 0;
+    int window = 4;      // of this wave's last list (direct_row)
+    bool quick = true;   // this wave looks at 512 columns before a whole row
+    uint32_t block = 8;
     __syncthreads();
     for (;;) {
         const uint32_t nF = S.nF[cur];
@@ -233,9 +325,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX> &
             status = 1;
             break;
         }
-        // watchdog: a cold start needs at most (2n(K + 2) - n) / (T + 1)
-        // phases (Lemma 3.2 with eq. (4)); more means a fault
-        if (phases >= bound) {
+        if (bound > 0 && phases >= bound) {
             status = -4;
             if (tid == 0)
                 __hip_atomic_fetch_or(A.err, 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -244,90 +334,293 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX> &
         phases += 1;
         sum_free += nF;
         const int nx = cur ^ 1;
-        for (uint32_t i = tid; i < nF; i += kBatchThreads) {
-            S.ab[0][i] = S.F[cur][i];
-            S.ap[0][i] = 0;
+        if (r + (uint32_t)n + 2u >= kKeyRounds) {
+            for (int i = tid; i < n; i += NT) S.key[i] = 0u;
+            r = 0;
+        }
+        // The rows of B' sorted by what they need: nothing (no column can be
+        // admissible: exhausted as a scan would be), their list, or their row.
+        for (uint32_t i0 = wave * 64; i0 < nF; i0 += NT) {
+            const bool in = i0 + lane < nF;
+            int b = 0, need = 0;
+            bool skip = false, listed = false;
+            if (in) {
+                b = S.F[cur][i0 + lane];
+                need = (int)S.y[b] - 1;
+                skip = need < (int)S.minv[b];
+                listed = !skip && need < (int)S.V[b];
+            }
+            const uint32_t f = wave_push(&S.nF[nx], skip);
+            const uint32_t l = wave_push(&S.nl[q], listed);
+            const uint32_t dd = wave_push(&S.nd[q], in && !skip && !listed);
+            if (skip) {
+                S.y[b] = (uint16_t)(need + 2);
+                S.F[nx][f] = (uint16_t)b;
+                scanned += (unsigned long long)n;
+            } else if (in) {
+                const uint32_t at = listed ? l : (uint32_t)(NMAX - 1) - dd;
+                S.ab[q][at] = (uint16_t)b;
+                S.ap[q][at] = 0;
+            }
         }
         __syncthreads();
-        if (tid == 0) {
-            S.nact[0] = nF;
-            S.nF[nx] = 0;
-            S.nL = 0;
-        }
-        const uint32_t r0 = r + 1;
-        int ac = 0;
         int64_t phase_rounds = 0;
         for (;;) {
             r += 1;
-            if (tid == 0) S.P = S.D = 0;
-            __syncthreads();
-            const uint32_t nact = S.nact[ac];
+            const uint32_t nl = S.nl[q], nd = S.nd[q];
             const int64_t t_start = timed ? (int64_t)wall_clock64() : 0;
-            // widest lane groups that still give every active row its own group
-            if (nact > (uint32_t)kBatchThreads / 16)
-                round_pass<4, NMAX>(S, k, ldk, n, A.origin, r0, r, ac, nx);
-            else if (nact > (uint32_t)kBatchThreads / 64)
-                round_pass<16, NMAX>(S, k, ldk, n, A.origin, r0, r, ac, nx);
-            else
-                round_pass<64, NMAX>(S, k, ldk, n, A.origin, r0, r, ac, nx);
-            __syncthreads();
+            if (tid == 0) {
+                // read by everyone before the last barrier, next used after
+                // the coming one
+                S.nl[q ^ 1] = S.nd[q ^ 1] = S.prop[q ^ 1] = 0;
+                S.nF[cur] = 0;
+            }
+            // Rows without a list: one wave each, up to 64 of the wave's rows at
+            // a time (8 at first, to find out which way suits them). Where admissible columns are many (rows that overflow
+            // their lists) the 512 columns from the row's position usually
+            // hold one: `quick` looks there first and leaves the misses to
+            // the whole-row pass. It is on while at least half its rows hit,
+            // and comes back when half the rows of a whole-row pass overflow.
+            int rows;
+            for (uint32_t i0 = wave; i0 < nd; i0 += kWaves * rows) {
+                rows = (int)min(block, (nd - i0 + kWaves - 1) / kWaves);
+                block = 64u;
+                unsigned long long left = rows == 64 ? ~0ull : (1ull << rows) - 1ull;
+                auto slot = [&](int e) { return NMAX - 1 - (int)i0 - e * kWaves; };
+                if (quick) {
+                    auto start_of = [&](int b, int pos) {
+                        int c = (A.origin == 0 ? b : 0) + pos;
+                        return c >= n ? c - n : c;
+                    };
+                    auto load_window = [&](int e, int *b, int *c) {
+                        *b = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(e)]);
+                        *c = start_of(*b, __builtin_amdgcn_readfirstlane((int)S.ap[q][slot(e)]));
+                        const int col0 = (*c & ~7) + lane * 8;
+                        return col0 < n ? *reinterpret_cast<const uint4 *>(k + (int64_t)*b * ldk + col0)
+                                        : make_uint4(~0u, ~0u, ~0u, ~0u);
+                    };
+                    int bn, cn;
+                    uint4 kn = load_window(0, &bn, &cn);
+                    for (int e = 0; e < rows; ++e) {
+                        const int b = bn, c = cn, at = slot(e);
+                        const uint4 kv = kn;
+                        if (e + 1 < rows) kn = load_window(e + 1, &bn, &cn);
+                        const int need = __builtin_amdgcn_readfirstlane((int)S.y[b] - 1);
+                        const int col0 = (c & ~7) + lane * 8;
+                        // a scan that started at origin + pos wraps at n and ends
+                        // before its origin
+                        const int origin = A.origin == 0 ? b : 0;
+                        const int end = c < origin ? origin : n;
+                        uint32_t m = 0;
+                        if (col0 < end)
+                            m = match_mask(kv, *reinterpret_cast<const uint4 *>(&S.t[col0]), need) &
+                                range_mask(col0, c, end);
+                        const unsigned long long bal = __ballot(m != 0u);
+                        if (bal == 0ull) continue;
+                        left &= ~(1ull << e);
+                        const int L = __builtin_ctzll(bal);
+                        const int a = (c & ~7) + L * 8 +
+                                      __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)m, L));
+                        if (lane != 0) continue;
+                        const int j = a >= origin ? a - origin : a - origin + n;
+                        scanned += (unsigned long long)(j - (int)S.ap[q][at] + 1);
+                        S.pa[at] = (uint16_t)a;
+                        S.ap[q][at] = (uint16_t)j;
+                        S.prop[q] = 1;
+                        atomicMax(&S.key[a], batch_key(r, b));
+                    }
+                    quick = 2 * __builtin_popcountll(left) <= rows;
+                }
+                // whole rows; the next row's loads in flight while one is compared
+                if (left == 0ull) continue;
+                int en = __builtin_ctzll(left), overflowed = 0;
+                const int full = __builtin_popcountll(left);
+                int bn = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(en)]);
+                RowRegs<NC> kn = load_row<NC>(k + (int64_t)bn * ldk, n, lane);
+                // A row's list is stored while the next row is looked at,
+                // before the loads of the row after that: the wait for those
+                // loads then does not wait for a store just issued.
+                int stored = -1;
+                auto store_list = [&]() {
+                    if (stored >= 0 && lane < kListLanes)
+                        *reinterpret_cast<uint4 *>(lists + (int64_t)stored * kListCap + lane * 4) =
+                            *reinterpret_cast<const uint4 *>(&S.stage[wave][lane * 4]);
+                };
+                while (left) {
+                    const int b = bn, at = slot(en);
+                    const RowRegs<NC> kr = kn;
+                    left &= left - 1ull;
+                    store_list();
+                    if (left) {
+                        en = __builtin_ctzll(left);
+                        bn = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(en)]);
+                        kn = load_row<NC>(k + (int64_t)bn * ldk, n, lane);
+                    }
+                    const int need = __builtin_amdgcn_readfirstlane((int)S.y[b] - 1);
+                    const int pos = S.ap[q][at];
+                    const int origin = A.origin == 0 ? b : 0;
+                    uint16_t minv, V;
+                    const Hit h = direct_row<NC>(kr, S.t, n, origin, need, lane, S.stage[wave],
+                                                 &minv, &V, &window);
+                    stored = V ? b : -1;
+                    overflowed += V == 0;
+                    if (lane != 0) continue;
+                    S.V[b] = V;
+                    S.pa[at] = (uint16_t)h.a;
+                    if (h.j >= 0) {
+                        scanned += (unsigned long long)(h.j - pos + 1);
+                        S.ap[q][at] = (uint16_t)h.j;
+                        S.prop[q] = 1;
+                        atomicMax(&S.key[h.a], batch_key(r, b));
+                    } else {
+                        scanned += (unsigned long long)(n - pos);
+                        S.pm[at] = minv;
+                    }
+                }
+                store_list();
+                if (2 * overflowed >= full) quick = true;
+            }
+            // rows with a list: kListLanes lanes each
+            for (uint32_t i0 = wave * (64 / kListLanes); i0 < nl; i0 += NT / kListLanes) {
+                const uint32_t i = i0 + (uint32_t)(lane / kListLanes);
+                const bool in = i < nl;
+                int b = 0, need = 0, pos = 0, origin = 0;
+                uint32_t j = 0x7FFFFFFFu, lo = 0x7FFFFFFFu;
+                if (in) {
+                    b = S.ab[q][i];
+                    const uint4 e = *reinterpret_cast<const uint4 *>(
+                        lists + (int64_t)b * kListCap + (lane % kListLanes) * 4);
+                    need = (int)S.y[b] - 1;
+                    pos = S.ap[q][i];
+                    origin = A.origin == 0 ? b : 0;
+                    const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int a = (int)(ew[u] & 0xFFFFu);
+                        const uint32_t v = (ew[u] >> 16) + S.t[a];
+                        const uint32_t ja = (uint32_t)(a >= origin ? a - origin : a - origin + n);
+                        if (v == (uint32_t)need) j = min(j, ja);
+                        lo = min(lo, v);
+                    }
+                }
+                j = group8_min_u32(j);
+                lo = group8_min_u32(lo);
+                if (!in || lane % kListLanes != 0) continue;
+                if (j != 0x7FFFFFFFu) {
+                    const int a = origin + (int)j < n ? origin + (int)j : origin + (int)j - n;
+                    scanned += (unsigned long long)((int)j - pos + 1);
+                    S.pa[i] = (uint16_t)a;
+                    S.ap[q][i] = (uint16_t)j;
+                    S.prop[q] = 1;
+                    atomicMax(&S.key[a], batch_key(r, b));
+                } else {
+                    scanned += (unsigned long long)(n - pos);
+                    S.pa[i] = kNone16;
+                    S.pm[i] = (uint16_t)min(lo, (uint32_t)S.V[b]);  // v >= V off the list
+                }
+            }
+            // (the lists written are read after the next barrier at the earliest)
+            barrier_lds();
             if (timed && tid == 0 && 4u * r <= 3u * (uint32_t)kRoundTimeCap) {
                 A.rtime[4 * (r - 1)] = t_start;
                 A.rtime[4 * (r - 1) + 1] = (int64_t)wall_clock64();
-                A.rtime[4 * (r - 1) + 2] = nact;
+                A.rtime[4 * (r - 1) + 2] = nl + nd;
                 A.rtime[4 * (r - 1) + 3] = phases;
             }
-            const uint32_t P = S.P, D = S.D;
-            if (P > 0) phase_rounds += 1;
-            if (P == D) break;  // nobody lost a proposal: M' is maximal
-            if (tid == 0) S.nact[ac ^ 1] = 0;
-            __syncthreads();
-            for (uint32_t i = tid; i < nact; i += kBatchThreads) {
-                const int a = S.at[i];
-                if (a < 0) continue;
-                const int b = S.ab[ac][i];
-                const unsigned long long kn = ((unsigned long long)r << 32) | (uint32_t)~(uint32_t)b;
-                if (S.key[a] != kn) {  // lost: resume after the lost column
-                    const uint32_t j = atomicAdd(&S.nact[ac ^ 1], 1u);
-                    S.ab[ac ^ 1][j] = b;
-                    S.ap[ac ^ 1][j] = S.ap[ac][i] + 1;
+            if (S.prop[q]) phase_rounds += 1;
+            // Winners: step (II), the column's old mate is free in the next
+            // phase, and (III a) for the column, y(a) -= 1, at once: every
+            // slack v - need is >= 0, so raising t also takes the column out of
+            // every row's sight for the rest of the phase. Losers look on from
+            // one position after the column they lost. A row that found nothing
+            // stays free in M', (III b).
+            const uint32_t top = nl + nd;
+            for (uint32_t i0 = wave * 64; i0 < top; i0 += NT) {
+                const uint32_t i = i0 + lane;
+                const uint32_t at = i < nl ? i : (uint32_t)(NMAX - 1) - (i - nl);
+                int a = kNone16, b = 0;
+                int freed = kNone16;
+                bool won = false, lost = false, listed = false;
+                if (i < top) {
+                    a = S.pa[at];
+                    b = S.ab[q][at];
+                    if (a != kNone16) {
+                        won = S.key[a] == batch_key(r, b);
+                        lost = !won;
+                        if (won) {
+                            freed = S.mate[a];
+                            S.mate[a] = (uint16_t)b;
+                            S.t[a] = (uint16_t)(S.t[a] + 1u);
+                        } else {
+                            // (this round may just have given the row a list)
+                            listed = (int)S.y[b] - 1 < (int)S.V[b];
+                        }
+                    } else {
+                        freed = b;
+                        S.y[b] = (uint16_t)(S.y[b] + 1u);
+                        S.minv[b] = S.pm[at];
+                    }
+                }
+                const uint32_t f = wave_push(&S.nF[nx], freed != kNone16);
+                const uint32_t l = wave_push(&S.nl[q ^ 1], listed);
+                const uint32_t dd = wave_push(&S.nd[q ^ 1], lost && !listed);
+                if (freed != kNone16) S.F[nx][f] = (uint16_t)freed;
+                if (lost) {
+                    const uint32_t to = listed ? l : (uint32_t)(NMAX - 1) - dd;
+                    S.ab[q ^ 1][to] = (uint16_t)b;
+                    S.ap[q ^ 1][to] = (uint16_t)(S.ap[q][at] + 1);
                 }
             }
-            ac ^= 1;
             __syncthreads();
+            q ^= 1;
+            if (S.nl[q] + S.nd[q] == 0u) break;  // nobody lost a proposal: M' is maximal
         }
         rounds += phase_rounds;
         if (phase_rounds > max_rounds) max_rounds = phase_rounds;
-        // Step (III a): y(a) -= 1 on every column of M'.
-        const uint32_t nL = S.nL;
-        for (uint32_t i = tid; i < nL; i += kBatchThreads) S.t[S.L[i]] += 1;
         cur = nx;
-        __syncthreads();
     }
     const uint32_t nfree = S.nF[cur];
 
-    // Matching from the keys; the free rows are F[cur], the free columns the
+    // Matching from the mates; the free rows are F[cur], the free columns the
     // never-taken ones. Completion (Section 2.1): i-th free b (ascending)
     // with the i-th free a (ascending).
-    int32_t *mb = S.ap[0], *ma = S.ap[1];
-    for (int i = tid; i < n; i += kBatchThreads) {
-        mb[i] = -1;
-        S.at[i] = 0;
+    uint16_t *mb = S.ap[0], *ma = S.ap[1];
+    for (int i = tid; i < n; i += NT) {
+        mb[i] = kNone16;
+        S.pa[i] = 0;
     }
     __syncthreads();
-    for (int i = tid; i < n; i += kBatchThreads) {
-        const unsigned long long kk = S.key[i];
-        const int32_t b = kk ? (int32_t)~(uint32_t)kk : -1;
+    for (int i = tid; i < n; i += NT) {
+        const uint16_t b = S.mate[i];
         ma[i] = b;
-        if (b >= 0) mb[b] = i;
+        if (b != kNone16) mb[b] = (uint16_t)i;
     }
-    for (uint32_t i = tid; i < nfree; i += kBatchThreads) S.at[S.F[cur][i]] = 1;
+    for (uint32_t i = tid; i < nfree; i += NT) S.pa[S.F[cur][i]] = 1;
     __syncthreads();
+    // ascending list of the i < n with flag(i), by all threads
+    auto ordered_list = [&](auto flag, uint16_t *out) {
+        int base = 0;
+        for (int i0 = 0; i0 < n; i0 += NT) {
+            const bool f = i0 + tid < n && flag(i0 + tid);
+            const unsigned long long bal = __ballot(f);
+            if (lane == 0) S.wcnt[wave] = (uint32_t)__popcll(bal);
+            __syncthreads();
+            int before = base, total = base;
+            for (int w = 0; w < kWaves; ++w) {
+                if (w < wave) before += (int)S.wcnt[w];
+                total += (int)S.wcnt[w];
+            }
+            if (f) out[before + (int)lanes_below(bal)] = (uint16_t)(i0 + tid);
+            base = total;
+            __syncthreads();
+        }
+        return base;
+    };
     if (A.complete && status >= 0) {
-        const int nb = ordered_list(S, n, [&](int i) { return S.at[i] != 0; }, S.ab[0]);
-        const int na = ordered_list(S, n, [&](int i) { return S.key[i] == 0ull; }, S.ab[1]);
+        const int nb = ordered_list([&](int i) { return S.pa[i] != 0; }, S.ab[0]);
+        const int na = ordered_list([&](int i) { return S.mate[i] == kNone16; }, S.ab[1]);
         const int m = min(nb, na);
-        for (int i = tid; i < m; i += kBatchThreads) {
+        for (int i = tid; i < m; i += NT) {
             mb[S.ab[0][i]] = S.ab[1][i];
             ma[S.ab[1][i]] = S.ab[0][i];
         }
@@ -338,56 +631,63 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX> &
     const float *X = A.X + off * A.d, *Y = A.Y + off * A.d;
     long long ks = 0;
     double cs = 0.0;
-    for (int i = tid; i < n; i += kBatchThreads) {
-        A.mate_a[off + i] = ma[i];
-        A.mate_b[off + i] = mb[i];
+    for (int i = tid; i < n; i += NT) {
+        const int a = mb[i] == kNone16 ? -1 : (int)mb[i];
+        A.mate_a[off + i] = ma[i] == kNone16 ? -1 : (int)ma[i];
+        A.mate_b[off + i] = a;
         A.y_a[off + i] = -(int32_t)S.t[i];
-        A.y_b[off + i] = S.yb[i];
-        const int a = mb[i];
+        A.y_b[off + i] = S.y[i];
         if (a >= 0) {
             ks += k[(int64_t)i * ldk + a];
             double s = 0.0;
-            for (int q = 0; q < A.d; ++q) {
-                const double dq = __dsub_rn((double)X[(int64_t)i * A.d + q], (double)Y[(int64_t)a * A.d + q]);
+            for (int e = 0; e < A.d; ++e) {
+                const double dq = __dsub_rn((double)X[(int64_t)i * A.d + e], (double)Y[(int64_t)a * A.d + e]);
                 s = __dadd_rn(s, __dmul_rn(dq, dq));
             }
             cs = __dadd_rn(cs, s);
         }
     }
-    S.red_k[tid] = ks;
-    S.red_c[tid] = cs;
-    __syncthreads();
-    for (int o = kBatchThreads / 2; o > 0; o >>= 1) {
-        if (tid < o) {
-            S.red_k[tid] += S.red_k[tid + o];
-            S.red_c[tid] = __dadd_rn(S.red_c[tid], S.red_c[tid + o]);
-        }
-        __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        ks += __shfl_xor(ks, o);
+        cs = __dadd_rn(cs, __shfl_xor(cs, o));
+        scanned += __shfl_xor(scanned, o);
     }
+    if (lane == 0) {
+        S.red_k[wave] = ks;
+        S.red_c[wave] = cs;
+        S.red_s[wave] = scanned;
+    }
+    __syncthreads();
     if (tid == 0) {
+        for (int w = 1; w < kWaves; ++w) {
+            ks += S.red_k[w];
+            cs = __dadd_rn(cs, S.red_c[w]);
+            scanned += S.red_s[w];
+        }
         InstanceStats &st = A.stats[inst];
         const float m = A.m[inst];
         st.phases = phases;
         st.sum_free = sum_free;
         st.rounds = rounds;
         st.max_rounds = max_rounds;
-        st.scanned = (int64_t)S.scanned;
+        st.scanned = (int64_t)scanned;
         st.matched_in_phases = n - (int64_t)nfree;
         st.completed_pairs = A.complete ? (int64_t)nfree : 0;
-        st.sum_k = S.red_k[0];
+        st.sum_k = ks;
         st.threshold = T;
         st.status = status;
         st.kmax = m > 0.0f ? (int32_t)floor(1.0 / A.eps) : 0;
         st.cost_scale = (double)m;
-        st.cost = m > 0.0f ? S.red_c[0] / (double)m : 0.0;
+        st.cost = m > 0.0f ? cs / (double)m : 0.0;
     }
     __syncthreads();
 }
 
-template <int NMAX>
-__global__ void __launch_bounds__(kBatchThreads) batch_solve_kernel(BatchArgs A)
+template <int NMAX, int NT>
+// (4 waves per SIMD: two workgroups of 512 threads or one of 1,024 a CU)
+__global__ void __launch_bounds__(NT, 4) batch_solve_kernel(BatchArgs A)
 {
-    __shared__ BatchShared<NMAX> S;
+    __shared__ BatchShared<NMAX, NT> S;
     for (;;) {
         if (threadIdx.x == 0)
             S.job = (int32_t)__hip_atomic_fetch_add(A.queue, 1u, __ATOMIC_RELAXED,
@@ -396,11 +696,20 @@ __global__ void __launch_bounds__(kBatchThreads) batch_solve_kernel(BatchArgs A)
         const int job = S.job;
         __syncthreads();
         if (job >= A.batch) break;
-        solve_instance<NMAX>(A, A.order[job], S, A.rtime != nullptr && job == 0);
+        solve_instance<NMAX, NT>(A, A.order[job], S, A.rtime != nullptr && job == 0);
     }
 }
 
 __global__ void batch_reset_kernel(unsigned int *queue) { *queue = 0u; }
+
+// The variant for a batch: n_max picks the LDS layout.
+template <class F>
+auto with_batch_kernel(int32_t n_max, int32_t batch, F f)
+{
+    if (n_max > 1024) return f(batch_solve_kernel<2048, 1024>, 1024);
+    return batch > kBatchWideMax ? f(batch_solve_kernel<1024, 512>, 512)
+                                 : f(batch_solve_kernel<1024, 1024>, 1024);
+}
 
 }  // namespace
 
@@ -409,11 +718,9 @@ int32_t batch_max_n() { return 2048; }
 hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid)
 {
     int per_cu = 0, dev = 0, cus = 0;
-    hipError_t e = n_max <= 1024
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_solve_kernel<1024>,
-                                                       kBatchThreads, 0)
-        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_solve_kernel<2048>,
-                                                       kBatchThreads, 0);
+    hipError_t e = with_batch_kernel(n_max, batch, [&](auto fn, int threads) {
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
+    });
     if (e != hipSuccess) return e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
@@ -428,10 +735,10 @@ hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipSt
 {
     hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, s, a.queue);
     if (a.batch == 0) return hipGetLastError();
-    if (n_max <= 1024)
-        hipLaunchKernelGGL(batch_solve_kernel<1024>, dim3(grid), dim3(kBatchThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(batch_solve_kernel<2048>, dim3(grid), dim3(kBatchThreads), 0, s, a);
+    with_batch_kernel(n_max, a.batch, [&](auto fn, int threads) {
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, s, a);
+        return 0;
+    });
     return hipGetLastError();
 }
 

@@ -71,6 +71,50 @@ __device__ inline uint32_t lanes_below(unsigned long long mask)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Wave-wide reductions and scans on the cross-lane paths of the vector ALU
+// (DPP), a few cycles a step where a shuffle through LDS takes tens.
+template <int kCtrl, int kRows = 0xF>
+__device__ inline uint32_t dpp_u32(uint32_t identity, uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, kCtrl, kRows, 0xF, false);
+}
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+
+// lane i: v(0) + ... + v(i)
+__device__ inline uint32_t wave_inclusive_sum_u32(uint32_t v)
+{
+    v += dpp_u32<kDppShr1>(0u, v);
+    v += dpp_u32<kDppShr2>(0u, v);
+    v += dpp_u32<kDppShr4>(0u, v);
+    v += dpp_u32<kDppShr8>(0u, v);
+    v += dpp_u32<kDppBcast15, 0xA>(0u, v);
+    v += dpp_u32<kDppBcast31, 0xC>(0u, v);
+    return v;
+}
+__device__ inline uint32_t wave_sum_u32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum_u32(v), 63);
+}
+__device__ inline uint32_t wave_min_u32(uint32_t v)
+{
+    v = min(v, dpp_u32<kDppShr1>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppShr2>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppShr4>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppShr8>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppBcast15, 0xA>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppBcast31, 0xC>(0xFFFFFFFFu, v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// minimum over each group of 8 lanes, in all of them
+__device__ inline uint32_t group8_min_u32(uint32_t v)
+{
+    v = min(v, dpp_u32<kDppXor1>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppXor2>(0xFFFFFFFFu, v));
+    return min(v, dpp_u32<kDppHalfMirror>(0xFFFFFFFFu, v));
+}
+
 struct Hit {
     int j;  // scan position of the hit, -1 if the row is exhausted
     int a;  // its column

@@ -147,6 +147,8 @@ struct BatchArgs {
     int32_t *mate_a, *mate_b, *y_a, *y_b;
     InstanceStats *stats;
     unsigned int *queue;
+    uint32_t *lists;          // kBatchListCap entries per row (packed rows): candidate lists
+    int64_t phase_bound;      // watchdog: 0 the safe bound, > 0 that many phases, < 0 none
     int64_t *rtime;           // optional diagnostics: 4 int64 per round of the first job
     int32_t *err;             // bit 8: an instance was stopped by the phase-bound watchdog
 };
@@ -192,6 +194,7 @@ hipError_t launch_points_mfma(const PointsJob &j, const MfmaAux &x, int64_t n_ma
                               int64_t ldk_max, hipStream_t s);
 
 // batch.hip
+constexpr int kBatchListCap = 32;
 int32_t batch_max_n();
 hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid);
 hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipStream_t s);
