@@ -770,7 +770,7 @@ int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
         nl += (int64_t)4 * G * n_arr[i];
         ns += 2 * (int64_t)n_arr[i];
     }
-    const int64_t words_per = (int64_t)3 * prot::kMaxGroups * prot::kWordStride;
+    const int64_t words_per = (int64_t)prot::kWordRing * prot::kMaxGroups * prot::kWordStride;
     int rc = dev_alloc(c, &bp->t_key, (size_t)nk);
     if (!rc) rc = dev_alloc(c, &bp->t_t, (size_t)nt);
     if (!rc) rc = dev_alloc(c, &bp->t_lists, (size_t)nl);
@@ -975,7 +975,7 @@ int prot_ctx_create(prot_ctx **out, int device, void *hip_stream)
         c->part_k = c->rep->part_k;
         c->part_c = c->rep->part_c;
     }
-    if (!rc) rc = dev_alloc(c, &c->words, (size_t)3 * prot::kMaxGroups * prot::kWordStride);
+    if (!rc) rc = dev_alloc(c, &c->words, (size_t)prot::kWordsTotal);
     if (!rc) rc = dev_alloc(c, &c->trace, (size_t)4 * prot::kTraceCap);
     if (!rc && hipHostMalloc((void **)&c->stage, sizeof(prot_ctx::Stage), hipHostMallocDefault) !=
                    hipSuccess)

@@ -21,6 +21,13 @@ __device__ inline T add_agent(T *p, T v)
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The XCD this wave runs on (hardware register XCC_ID, id 20, all 32 bits).
+constexpr uint32_t kXcds = 8;
+__device__ inline uint32_t xcd_id()
+{
+    return (uint32_t)__builtin_amdgcn_s_getreg(20 | (31 << 11)) % kXcds;
+}
+
 // bit e set iff lo <= col0 + e < hi, for e in [0, 8)
 __device__ inline uint32_t range_mask(int col0, int lo, int hi)
 {

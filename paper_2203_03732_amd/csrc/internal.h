@@ -38,15 +38,23 @@ struct alignas(128) Ctl {
 // Error bits of a phase loop that leave its state unusable.
 constexpr int32_t kErrLoop = 4 | 8 | 32 | 64;
 constexpr int kLoopThreads = 1024;      // threads per workgroup of the loop
-// Round barrier: the workgroups are split into up to kMaxGroups groups
-// (blockIdx % G); each round has one word per group, kWordStride words
-// apart (one 128-byte line each), in a ring of three rounds: round r uses
-// words[(r % 3) * kMaxGroups * kWordStride + g * kWordStride]. Workgroup 0
-// clears the words of round r + 1 during round r, after every reader of
-// their previous use (round r - 2) has passed a barrier. Each list of the
-// loop is split into G regions of list_cap entries, one per group.
+// Round barrier: the workgroups are split into up to kMaxGroups groups (by
+// the XCD they run on); each round has one word per group, kWordStride words
+// apart (one 128-byte line each), in a ring of kWordRing rounds: round r uses
+// words[(r % kWordRing) * kMaxGroups * kWordStride + g * kWordStride]. The
+// first workgroup of a group to arrive in round r clears the group's word of
+// round r + 2. Each list of the loop is split into G regions of list_cap
+// entries, one per group.
+constexpr int kWordRing = 4;
 constexpr int kMaxGroups = 32;
 constexpr int kWordStride = 16;
+// After the words of the ring, for a single instance: the groups' sums as
+// published, per round of the ring and reading XCD kMaxGroups slots, and the
+// launch's registration (total, then per group).
+constexpr int kPublished = kWordRing * kMaxGroups * kWordStride;
+constexpr int kXcdsMax = 8;
+constexpr int kRegistered = kPublished + kWordRing * kXcdsMax * kMaxGroups;
+constexpr int kWordsTotal = kRegistered + 1 + kMaxGroups;
 constexpr int kTraceCap = 65536;        // phases recorded in the trace
 constexpr int kFinalizeBlocks = 256;    // partial sums of the finalize kernel
 // Per-block maxima of the single-instance maximum pass (d = 2, 3): at most
@@ -85,7 +93,7 @@ struct LoopArgs {
     int64_t list_cap;         // entries per group region of F and L (>= n)
     int32_t groups;           // G, 1 <= G <= min(kMaxGroups, grid)
     int32_t pad2;
-    unsigned long long *words;  // round words, 3 * kMaxGroups * kWordStride
+    unsigned long long *words;  // round words (kWordsTotal; teams: the ring only)
     int64_t y_off;            // batched teams: y_b is the launch's y_b base + y_off
     Ctl *ctl;
     int64_t *trace;           // 4 int64 per phase

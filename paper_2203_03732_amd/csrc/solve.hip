@@ -68,6 +68,10 @@ constexpr int kSpinLimit = 1 << 22;            // bounded waits for list entries
 // bounded, so the grid drains).
 constexpr int64_t kBarrierTicks = 1000000000ll;
 constexpr int32_t kDualMax = 0x7FFF;           // t (-y(a)) fits its 15-bit field
+// Proposals are combined within a workgroup from this many rows still looking.
+constexpr uint32_t kCombineMin = 16;
+constexpr uint32_t kPublishMin = 128;   // workgroups from which barrier sums are published
+constexpr uint32_t kCombineSlots = 64;  // (768 bytes of LDS)
 constexpr int kGateSpin = 256;                 // gate polls (~0.3 ms) before it closes early
 
 // Waits until this wave's earlier stores and atomics have completed.
@@ -516,7 +520,7 @@ __device__ int team_scan(const Src &src, const typename Src::Row &row, const uin
 __global__ void loop_reset_kernel(LoopArgs a)
 {
     Ctl *c = a.ctl;
-    for (int i = 0; i < 3 * kMaxGroups; ++i) a.words[i * kWordStride] = 0ull;
+    for (int i = 0; i < kWordsTotal; ++i) a.words[i] = 0ull;
     c->gate_count = 0;
     c->gate = 0;
     c->free0 = 0;
@@ -537,8 +541,10 @@ __global__ void loop_reset_kernel(LoopArgs a)
 __global__ void init_kernel(LoopArgs a, int32_t warm, const int32_t *mate_a,
                             int32_t *mate_b, const int32_t *y_a)
 {
-    if (!warm && blockIdx.x == 0 && threadIdx.x < 3 * kMaxGroups)
-        a.words[threadIdx.x * kWordStride] = 0ull;
+    if (!warm)
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < kWordsTotal;
+             i += gridDim.x * blockDim.x)
+            a.words[i] = 0ull;
     if (!warm && blockIdx.x == 0 && threadIdx.x == 0) {
         Ctl *c = a.ctl;
         c->gate_count = 0;
@@ -751,7 +757,11 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
     __shared__ int s_mn[kLoopThreads / kWave];  // team mode: smallest k + t of a row's scan
     // regrouping into teams within a phase: rows still looking (by round
     // parity), slot of the next row handed over, the rows' scan states
-    __shared__ uint32_t s_nact[2], s_kact;
+    __shared__ uint32_t s_nact[2], s_kact, s_gsize;
+    // proposals combined within the workgroup: a slot's column (tagged with
+    // the round) and the largest key proposed to it
+    __shared__ uint32_t s_ccol[kCombineSlots];
+    __shared__ unsigned long long s_ckey[kCombineSlots];
     __shared__ int4 s_act[kLoopThreads / kWave / 2];
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -764,7 +774,41 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
     const int na = A.n_a;  // columns, |A| >= |B| (Section 3.3)
 
     const int G = A.groups;
-    const int grp = (int)(wg % (uint32_t)G);
+    // Barrier group: the XCD the workgroup runs on, so that a group's word is
+    // added to from one XCD. With many workgroups (publish) nobody polls the
+    // words: a group's last arrival publishes its sum. Polling takes a word's
+    // line to every XCD, and an arrival while others poll takes ~1.2 us
+    // instead of ~0.6; but the sum is seen ~0.3 us later, so that few
+    // workgroups, which arrive together, poll the words (a solve of ~1,000
+    // rows, 63 workgroups: 3% faster so; the n = 10,000 Euclidean loop of 256
+    // workgroups 10.2 -> 9.8 ms by publishing).
+    const bool publish = !kMulti && nwg >= kPublishMin;
+    const uint32_t xcd = kMulti ? 0u : xcd_id();
+    const int grp = (int)(kMulti ? wg % (uint32_t)G
+                                 : (xcd + kXcds * (wg % (uint32_t)((G + kXcds - 1) / kXcds))) %
+                                       (uint32_t)G);
+    if (publish) {
+        // how many workgroups of this launch are in the group: everyone
+        // registers once (all of them are resident, so the wait ends; it is
+        // bounded like the round barrier's)
+        if (threadIdx.x == 0) {
+            unsigned long long *reg = A.words + kRegistered;
+            add_agent(reg + 1 + grp, 1ull);
+            wait_memory();
+            add_agent(reg, 1ull);
+            const int64_t t_wait = (int64_t)wall_clock64();
+            while (ld_agent(reg) < nwg) {
+                if ((int64_t)wall_clock64() - t_wait >
+                    (A.barrier_ticks > 0 ? A.barrier_ticks : kBarrierTicks)) {
+                    __hip_atomic_fetch_or(&ctl->err, 32, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            s_gsize = (uint32_t)ld_agent(reg + 1 + grp);
+        }
+    }
     const int64_t cap = A.list_cap;  // entries per group region of a list
 
     for (int i = threadIdx.x; i < A.n_pad; i += blockDim.x) t_lds[i] = A.t[i];
@@ -776,6 +820,10 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
         s_pend_scan = 0;
         s_nact[0] = s_nact[1] = 0;
         s_kact = 0;
+    }
+    if (threadIdx.x < kCombineSlots) {
+        s_ccol[threadIdx.x] = 0u;
+        s_ckey[threadIdx.x] = 0ull;
     }
     if (threadIdx.x < kMaxGroups) {
         // the first free list is one region (group 0)
@@ -907,6 +955,7 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
         unsigned long long active = __ballot((uint32_t)lane < nslots) & ~pre;
         unsigned long long wave_scan = 0;
         bool first_round = true;
+        bool combine = false;  // proposals of this workgroup meet in LDS first
 
         for (;;) {
             r += 1;
@@ -937,10 +986,10 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                 // so its scans stay short and teams only add overhead)
                 constexpr bool kRegroup = !kCopies;
                 const bool counts = R == 1 ? (active != 0ull) : (k_rank == 0 && (active & 1ull));
-                if (kRegroup && R < 16 && lane == 0 && counts)
+                if (R < 16 && lane == 0 && counts)
                     atomicAdd(&s_nact[r & 1], R == 1 ? (uint32_t)__popcll(active) : 1u);
                 __syncthreads();
-                if (kRegroup && R < 16) {
+                if (R < 16) {
                     // Once the workgroup's rows still looking fit in half its
                     // waves per team (or, in slot mode, in half its waves),
                     // the phase continues with teams twice as large or more
@@ -949,7 +998,8 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                     // Which waves scan a row does not change what they find.
                     const uint32_t nact = __builtin_amdgcn_readfirstlane(s_nact[r & 1]);
                     if (threadIdx.x == 0) s_nact[(r + 1) & 1] = 0;
-                    if (nact > 0u && 2u * (uint32_t)R * nact <= (uint32_t)wpg) {
+                    combine = R == 1 && nact >= kCombineMin;
+                    if (kRegroup && nact > 0u && 2u * (uint32_t)R * nact <= (uint32_t)wpg) {
                         const bool mine_row = R == 1 ? ((active >> lane) & 1ull) != 0ull
                                                      : (k_rank == 0 && lane == 0 && (active & 1ull));
                         if (mine_row)
@@ -1026,11 +1076,7 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                         const unsigned long long kn = make_key(r, b, yb, P);
                         if (lead) {
                             wave_scan += (unsigned long long)(j - pos + 1);
-                            if (lane == 0) {
-                                s_old = __hip_atomic_fetch_max(A.key + a, kn, __ATOMIC_RELAXED,
-                                                               __HIP_MEMORY_SCOPE_AGENT);
-                                proposed = true;
-                            }
+                            proposed = lane == 0;
                             n_prop = 1;
                         }
                         if (lane == 0) {
@@ -1104,10 +1150,6 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                         wave_scan += (unsigned long long)(h.j - pos + 1);
                         const unsigned long long kn = make_key(r, b, yb, P);
                         if (lane == s) {
-                            // the slot's own lane proposes, so proposals of several
-                            // slots are in flight together
-                            s_old = __hip_atomic_fetch_max(A.key + h.a, kn, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT);
                             proposed = true;
                             s_pos = h.j;
                             s_a = h.a;
@@ -1129,6 +1171,38 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                     }
                 }
             }
+            // The proposals of the wave's slots go out as one instruction, each
+            // slot's lane its own. Where many rows of a workgroup lost the last
+            // round, rows tend to follow each other from one column to the
+            // next, thousands to a column: an atomic on one address takes ~9 ns,
+            // so 4,000 of them take 35 us whoever waits. Then the workgroup's
+            // proposals to a column meet in LDS and only the largest key goes
+            // out (the others have lost); a column whose table slot is held by
+            // another column goes out directly.
+            bool send = proposed;
+            if (combine) {
+                const uint32_t slot = (uint32_t)s_a % kCombineSlots;
+                const uint32_t mine = (r << 18) | ((uint32_t)s_a & 0x3FFFFu);
+                bool held = false;
+                if (send) {
+                    const uint32_t cur = s_ccol[slot];
+                    uint32_t owner = cur;
+                    if ((cur ^ mine) >> 18) {
+                        owner = atomicCAS(&s_ccol[slot], cur, mine);
+                        if (owner == cur) owner = mine;
+                    }
+                    held = owner == mine;
+                    if (held) atomicMax(&s_ckey[slot], s_key);
+                }
+                __syncthreads();
+                if (held && s_ckey[slot] != s_key) {
+                    send = false;
+                    s_old = s_key;  // not the column's first proposal
+                }
+            }
+            if (send)
+                s_old = __hip_atomic_fetch_max(A.key + s_a, s_key, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
             // The first proposal to a column in a round: the column is in M'
             // whoever wins it, so step (II) evicts its old mate (if any) and
             // the column joins this phase's taken list.
@@ -1161,18 +1235,11 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
             // group that arrived before this one, which places this
             // workgroup's entries in the group's list regions.
             const bool timed = A.rtime != nullptr && r <= (uint32_t)kRoundTimeCap;
-            unsigned long long *words = A.words + (r % 3) * kMaxGroups * kWordStride;
+            unsigned long long *words = A.words + (r % kWordRing) * kMaxGroups * kWordStride;
             if (threadIdx.x < kWave) {
                 const int64_t t_arrive = timed ? (int64_t)wall_clock64() : 0;
-                // the words of round r + 1 were last read in round r - 2, which
-                // every workgroup has left
-                if (wg == 0) {
-                    if (lane < G)
-                        st_agent(A.words + ((r + 1) % 3) * kMaxGroups * kWordStride +
-                                     lane * kWordStride,
-                                 0ull);
-                    wait_memory();
-                }
+                unsigned long long sum = 0ull;  // of the group so far
+                bool last = false;
                 if (threadIdx.x == 0) {
                     const unsigned long long add = (1ull << kShiftArrive) |
                                                    ((unsigned long long)s_lose << kShiftLose) |
@@ -1183,11 +1250,36 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                         words + grp * kWordStride, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     s_base_l = s_lcum[grp] + (uint32_t)(o & kField);
                     s_base_f = s_fcum[grp] + (uint32_t)((o >> kShiftFree) & kField);
+                    // The first of its group to arrive clears the group's word
+                    // of round r + 2, last used in round r - 2, which every
+                    // workgroup has left. The store is complete before this
+                    // workgroup leaves the poll below, so before any
+                    // workgroup arrives in round r + 2.
+                    if ((uint32_t)(o >> kShiftArrive) == 0u)
+                        st_agent(A.words + ((r + 2) % kWordRing) * kMaxGroups * kWordStride +
+                                     grp * kWordStride,
+                                 0ull);
+                    sum = o + add;
+                    last = publish && (uint32_t)(sum >> kShiftArrive) == s_gsize;
+                }
+                // The group's last arrival publishes its sum to every XCD (and
+                // clears the slots of round r + 2, for the same reason).
+                if (__ballot(last)) {
+                    sum = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(
+                               (int)(sum >> 32))
+                           << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sum);
+                    if (lane < 2 * (int)kXcds)
+                        st_agent(A.words + kPublished +
+                                     (((r + (lane < (int)kXcds ? 0u : 2u)) % kWordRing) * kXcds +
+                                      (uint32_t)lane % kXcds) *
+                                         kMaxGroups +
+                                     grp,
+                                 lane < (int)kXcds ? sum : 0ull);
+                }
+                if (threadIdx.x == 0) {
                     flush_scan();
-                    // the last arrival of each group records its time (one
-                    // atomic per group rather than per workgroup)
-                    if (timed && (uint32_t)(o >> kShiftArrive) + 1u ==
-                                     nwg / (uint32_t)G + ((uint32_t)grp < nwg % (uint32_t)G ? 1u : 0u))
+                    if (timed)
                         __hip_atomic_fetch_max(&A.rtime[3 * (r - 1)], t_arrive, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
                 }
@@ -1203,13 +1295,17 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                              tagged(tag, (int32_t)my_fv));
             }
             if (threadIdx.x < kWave) {
-                // lane j < G polls the word of group j until every workgroup
+                // lane j < G polls the sum of group j until every workgroup
                 // arrived, or the bounded wait runs out
+                const unsigned long long *sums =
+                    publish ? A.words + kPublished + ((r % kWordRing) * kXcds + xcd) * kMaxGroups
+                            : words;
+                const int stride = publish ? 1 : kWordStride;
                 unsigned long long v;
                 const int64_t t_wait = (int64_t)wall_clock64();
                 bool late = false;
                 for (int spins = 0;; ++spins) {
-                    v = lane < G ? ld_agent(words + lane * kWordStride) : 0ull;
+                    v = lane < G ? ld_agent(sums + lane * stride) : 0ull;
                     if (wave_sum((uint32_t)(v >> kShiftArrive)) == nwg) break;
                     if ((spins & 63) == 1 &&
                         (int64_t)wall_clock64() - t_wait >
@@ -1219,6 +1315,7 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                     }
                     __builtin_amdgcn_s_sleep(1);
                 }
+                wait_memory();  // the cleared word (the poll's loads waited longer)
                 if (late) {
                     if (lane == 0) {
                         __hip_atomic_fetch_or(&ctl->err, 32, __ATOMIC_RELAXED,
@@ -1566,7 +1663,7 @@ __global__ void team_init_kernel(TeamArgs T)
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         Ctl *c = a.ctl;
-        for (int i = 0; i < 3 * kMaxGroups; ++i) a.words[i * kWordStride] = 0ull;
+        for (int i = 0; i < kWordRing * kMaxGroups; ++i) a.words[i * kWordStride] = 0ull;
         c->free0 = (uint32_t)a.n;
         c->scanned = 0;
         c->status = 0;
