@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libprot.so")
-SOURCES = ["cost.hip", "cost_mfma.hip", "solve.hip", "batch.hip", "loss.hip", "ot.hip",
+SOURCES = ["cost.hip", "cost_l1.hip", "cost_mfma.hip", "solve.hip", "batch.hip", "loss.hip", "ot.hip",
            "ot_cluster.hip", "api.cpp"]
 ARCH = "gfx950"
 

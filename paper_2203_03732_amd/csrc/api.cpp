@@ -70,6 +70,8 @@ struct prot_ctx {
     int32_t cost_metric = PROT_METRIC_SQEUCLIDEAN;  // prot_set_cost_metric
     float *l1_buf = nullptr;         // normalised vectors of the L1 image cost
     int64_t l1_cap = 0;
+    uint32_t *l1_aux = nullptr;      // its screening pass
+    int64_t l1_aux_cap = 0;
     int loop_groups = 8;             // barrier groups of the phase loop (PROT_LOOP_GROUPS)
     float *mfma_buf = nullptr;       // amax, emax, tile maxima of the matrix-core build
     int64_t mfma_cap = 0;
@@ -385,6 +387,19 @@ prot::PointsJob points_job(prot_ctx *c, const float *X, const float *Y, int64_t 
     return j;
 }
 
+// The L1 image cost is screened on rounded vectors (cost_l1.hip) from this many
+// pixels a vector and pairs times pixels: below, the extra passes (~25 us) cost
+// more than they save (whole build, every pair by the definition / screened:
+// 4,000 x 4,000 of 32 pixels 74 / 90 us, 1,000 x 1,000 of 256 114 / 99, of 784
+// 245 / 163, 10,000 x 10,000 of 784 3,150 / 1,420) ...
+constexpr double kL1ScreenMin = 5e7;
+constexpr int32_t kL1ScreenMinD = 256;
+// ... and the share of pairs that the definition's own rounding may leave
+// unplaced when every pixel of every vector is nonzero (the rounding bound of a
+// distance, 2.4e-7 per pixel, over the width eps of a cell): the lists hold
+// three in a hundred.
+constexpr double kL1ScreenShare = 0.025;
+
 // The L1 image cost normalises X and Y into a workspace first.
 int setup_l1(prot_ctx *c, prot::PointsJob &j, int64_t n_b, int64_t n_a)
 {
@@ -399,6 +414,34 @@ int setup_l1(prot_ctx *c, prot::PointsJob &j, int64_t n_b, int64_t n_a)
     }
     j.l1_x = c->l1_buf;
     j.l1_y = c->l1_buf + n_b * (int64_t)j.d;
+    j.l1 = prot::L1Aux{};
+    if (j.d < kL1ScreenMinD || (double)n_b * (double)n_a * (double)j.d < kL1ScreenMin ||
+        2.4e-7 * (double)j.d > kL1ScreenShare * j.eps)
+        return PROT_OK;
+    // one block: flags, rounded vectors, bounds, counts and lists
+    const int64_t ldx = round_up(n_b, 128), ldy = round_up(n_a, 128), words = prot::l1_words(j.d);
+    const int64_t tx = (n_a + prot::kL1SettleTile - 1) / prot::kL1SettleTile;
+    const int64_t tiles = tx * ((n_b + prot::kL1SettleTile - 1) / prot::kL1SettleTile);
+    const int64_t d64 = round_up(j.d, 64), t64 = round_up(tiles, 64);
+    const int64_t q = (ldx + ldy) * words;
+    const int64_t total = 64 + d64 + q + ldx + ldy + t64 + tiles * prot::kL1ListCap;
+    if (total > c->l1_aux_cap || !c->l1_aux) {
+        int rc = dev_alloc(c, &c->l1_aux, (size_t)total);
+        if (rc) return rc;
+        c->l1_aux_cap = total;
+    }
+    uint32_t *p = c->l1_aux;
+    j.l1.meta = p;
+    j.l1.used = p + 64;
+    j.l1.qx = j.l1.used + d64;
+    j.l1.qy = j.l1.qx + ldx * words;
+    j.l1.ldx = ldx;
+    j.l1.ldy = ldy;
+    j.l1.ex = reinterpret_cast<float *>(j.l1.qy + ldy * words);
+    j.l1.ey = j.l1.ex + ldx;
+    j.l1.count = reinterpret_cast<uint32_t *>(j.l1.ey + ldy);
+    j.l1.list = j.l1.count + t64;
+    j.l1.tiles_x = tx;
     return PROT_OK;
 }
 
@@ -1036,6 +1079,7 @@ int prot_ctx_destroy(prot_ctx *c)
     (void)hipFree(c->rtime);
     (void)hipFree(c->mfma_buf);
     (void)hipFree(c->l1_buf);
+    (void)hipFree(c->l1_aux);
     (void)hipFree(c->loss_part);
     for (void *p : {(void *)c->ot.s_off, (void *)c->ot.d_off, (void *)c->ot.row_pt,
                     (void *)c->ot.col_pt, (void *)c->ot.ymax, (void *)c->ot.cnt,

@@ -591,14 +591,13 @@ constexpr int kTile = 64;
 constexpr int kTj = 16;
 
 template <int PASS, bool L1 = false>
-__global__ void __launch_bounds__(256) points_tile_kernel(PointsJob j)
+__device__ __forceinline__ void points_tile(const PointsJob &j, int64_t b0, int64_t a0)
 {
     __shared__ __align__(16) float xs[kTj][kTile + 4];
     __shared__ __align__(16) float ys[kTj][kTile + 4];
     __shared__ float red[4];
     const Instance in = j.instance(blockIdx.z);
     const int64_t n = in.n, na = in.na;  // rows, columns
-    const int64_t b0 = (int64_t)blockIdx.y * kTile, a0 = (int64_t)blockIdx.x * kTile;
     if (b0 >= n || a0 >= (PASS ? in.ldk : na)) return;
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
     const int d = j.d;
@@ -702,68 +701,24 @@ __global__ void __launch_bounds__(256) points_tile_kernel(PointsJob j)
     }
 }
 
-// Section 5's image cost: each vector divided by its sum (binary32, the sum
-// taken in coordinate order by one lane). kNormFloats coordinates of a block's
-// vectors are staged in LDS. Entries must be finite and nonnegative with a
-// positive finite sum (err bit 1 otherwise). Block 0 also records the cost
-// scale 2 (the L1 distance of two such vectors is at most 2) and K.
-constexpr int kNormFloats = 12288;
-
-__global__ void __launch_bounds__(256) l1_normalize_kernel(PointsJob j, const float *src,
-                                                           int64_t n, float *dst)
+template <int PASS, bool L1 = false>
+__global__ void __launch_bounds__(256) points_tile_kernel(PointsJob j)
 {
-    __shared__ float v[kNormFloats];
-    __shared__ float sums[64];
-    __shared__ int bad;
-    const int d = j.d;
-    const int per = min(64, kNormFloats / d);
-    const int64_t first = (int64_t)blockIdx.x * per;
-    if (first >= n) return;
-    const int cnt = (int)min<int64_t>(per, n - first);
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < cnt * d; i += blockDim.x) {
-        const float x = src[first * d + i];
-        if (!(x >= 0.0f && x <= FLT_MAX)) bad = 1;
-        v[i] = x;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < cnt) {
-        float t = 0.0f;
-        for (int q = 0; q < d; ++q) t = __fadd_rn(t, v[threadIdx.x * d + q]);
-        if (!(t > 0.0f && t <= FLT_MAX)) bad = 1;
-        sums[threadIdx.x] = t;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < cnt * d; i += blockDim.x)
-        dst[first * d + i] = __fdiv_rn(v[i], sums[i / d]);
-    if (threadIdx.x == 0) {
-        if (bad) __hip_atomic_fetch_or(j.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (blockIdx.x == 0) {
-            j.m[0] = 2.0f;
-            if (j.kmax_out) *j.kmax_out = (int32_t)floor(1.0 / j.eps);
-        }
-    }
+    points_tile<PASS, L1>(j, (int64_t)blockIdx.y * kTile, (int64_t)blockIdx.x * kTile);
 }
 
-void launch_points_l1(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
+// The settling tiles of the screened L1 build whose lists overflowed, every
+// pair by the definition: grid (tiles, kTile rows of a tile), each block the
+// tiles of one row.
+__global__ void __launch_bounds__(256) points_tile_overflow_kernel(PointsJob j)
 {
-    // one instance (the batched solver keeps the squared cost)
-    const int64_t nb = j.n_single, na = j.na_single ? j.na_single : j.n_single;
-    const int per = std::min(64, kNormFloats / j.d);
-    PointsJob jn = j;
-    jn.X = j.l1_x;
-    jn.Y = j.l1_y;
-    if (nb > 0)
-        hipLaunchKernelGGL(l1_normalize_kernel, dim3((unsigned)((nb + per - 1) / per)), dim3(256),
-                           0, s, j, j.X, nb, j.l1_x);
-    if (na > 0)
-        hipLaunchKernelGGL(l1_normalize_kernel, dim3((unsigned)((na + per - 1) / per)), dim3(256),
-                           0, s, j, j.Y, na, j.l1_y);
-    const unsigned rows = (unsigned)((n_max + kTile - 1) / kTile);
-    hipLaunchKernelGGL((points_tile_kernel<1, true>),
-                       dim3((unsigned)((ldk_max + kTile - 1) / kTile), rows, 1), dim3(256), 0, s,
-                       jn);
+    if (j.l1.count[blockIdx.x] <= (uint32_t)kL1ListCap) return;
+    const int64_t ty = blockIdx.x / j.l1.tiles_x, tx = blockIdx.x - ty * j.l1.tiles_x;
+    const int64_t b0 = ty * kL1SettleTile + (int64_t)blockIdx.y * kTile;
+    for (int64_t a0 = tx * kL1SettleTile; a0 < (tx + 1) * kL1SettleTile; a0 += kTile) {
+        points_tile<1, true>(j, b0, a0);
+        __syncthreads();
+    }
 }
 
 void launch_points_tiled(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
@@ -832,6 +787,23 @@ hipError_t launch_round_costs(const float *C, int64_t n, int64_t na, int64_t ldc
     return hipGetLastError();
 }
 
+// The image cost of normalised vectors, every pair by the definition.
+hipError_t launch_points_tile_l1(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
+{
+    hipLaunchKernelGGL((points_tile_kernel<1, true>),
+                       dim3((unsigned)((ldk_max + kTile - 1) / kTile),
+                            (unsigned)((n_max + kTile - 1) / kTile), 1),
+                       dim3(256), 0, s, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_points_tile_l1_overflow(const PointsJob &j, int64_t tiles, hipStream_t s)
+{
+    hipLaunchKernelGGL(points_tile_overflow_kernel,
+                       dim3((unsigned)tiles, (unsigned)(kL1SettleTile / kTile)), dim3(256), 0, s, j);
+    return hipGetLastError();
+}
+
 hipError_t launch_points(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
 {
     // The plain maximum pass of one instance (d = 2, 3) with per-block maxima
@@ -841,8 +813,8 @@ hipError_t launch_points(const PointsJob &j, int64_t n_max, int64_t ldk_max, hip
     if (!self_reset)
         hipLaunchKernelGGL(build_reset_kernel, dim3((j.batch + 255) / 256), dim3(256), 0, s, j);
     if (n_max == 0 || j.batch == 0) return hipGetLastError();
-    if (j.metric == 2) launch_points_l1(j, n_max, ldk_max, s);
-    else if (j.d == 2) launch_points_d<2>(j, n_max, ldk_max, s);
+    if (j.metric == 2) return launch_points_l1(j, n_max, ldk_max, s);
+    if (j.d == 2) launch_points_d<2>(j, n_max, ldk_max, s);
     else if (j.d == 3) launch_points_d<3>(j, n_max, ldk_max, s);
     else if (j.mfma.tile_max) return launch_points_mfma(j, j.mfma, n_max, ldk_max, s);
     else launch_points_tiled(j, n_max, ldk_max, s);

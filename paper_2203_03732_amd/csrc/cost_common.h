@@ -34,6 +34,18 @@ struct PruneAux {
     int32_t *cx, *cy;         // candidate indices (n each)
 };
 
+// Workspace of the screened L1 image cost (one instance; used when `used` is
+// set): see cost_l1.hip.
+struct L1Aux {
+    uint32_t *meta;            // [0] bits of the largest normalised value, [1] used pixels
+    uint32_t *used;            // d: 1 if some vector is nonzero there
+    uint32_t *qx, *qy;         // rounded vectors, word-major
+    int64_t ldx, ldy;          // their pitches (vectors, rounded up to 128)
+    float *ex, *ey;            // per vector: bound on its share of a distance's error
+    uint32_t *count, *list;    // per settling tile: unplaced pairs
+    int64_t tiles_x;           // settling tiles along the columns
+};
+
 struct PointsJob {
     const float *X, *Y;        // packed points; instance i starts at row pt_off[i]
     const int64_t *pt_off;     // device, per instance (null: one instance at row 0)
@@ -48,6 +60,7 @@ struct PointsJob {
     int32_t metric;
     int32_t k8;                // 1: write k as uint8 (K <= 253, padding 0xFF); single instance
     float *l1_x, *l1_y;        // metric 2: workspace for the normalised X and Y
+    L1Aux l1;                  // metric 2: workspace of the screening pass
     int32_t d;
     int32_t batch;
     double eps;

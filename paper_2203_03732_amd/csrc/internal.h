@@ -193,6 +193,16 @@ hipError_t launch_round_costs(const float *C, int64_t n, int64_t na, int64_t ldc
                               int16_t *k, int64_t ldk, Ctl *ctl, hipStream_t s, int k8 = 0);
 hipError_t launch_points(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s);
 
+hipError_t launch_points_tile_l1(const PointsJob &j, int64_t n_max, int64_t ldk_max,
+                                 hipStream_t s);
+hipError_t launch_points_tile_l1_overflow(const PointsJob &j, int64_t tiles, hipStream_t s);
+
+// cost_l1.hip
+constexpr int kL1SettleTile = 256;   // rows and columns of a settling tile
+constexpr int kL1ListCap = 2048;     // unplaced pairs it can list
+int64_t l1_words(int32_t d);         // words of a rounded vector
+hipError_t launch_points_l1(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s);
+
 // cost_mfma.hip
 constexpr int32_t kMfmaMinD = 16;          // d from which the matrix cores can be used
 constexpr int32_t kMfmaAutoD = 48;         // d from which PROT_COST_AUTO uses them

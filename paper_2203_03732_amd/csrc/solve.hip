@@ -1592,7 +1592,35 @@ finalize_kernel(int64_t n, const int32_t *mate_b, const int16_t *k, int64_t ldk,
     const int64_t lo = min<int64_t>(n, blockIdx.x * per), hi = min<int64_t>(n, lo + per);
     long long ks = 0;
     double cs = 0.0;
-    for (int64_t b = lo + threadIdx.x; b < hi; b += kFinalizeThreads) {
+    if (cost_kind == 4) {
+        // half the L1 distance of the vectors normalised to sum 1: long
+        // vectors, one wave per row (n = 10,000 images of 784 pixels: 240 us
+        // with one thread per row, ~39 of a block's 256 with work)
+        const int lane = threadIdx.x & 63;
+        for (int64_t b = lo + threadIdx.x / 64; b < hi; b += kFinalizeThreads / 64) {
+            const int32_t a = mate_b[b];
+            if (a < 0) continue;
+            double sx = 0.0, sy = 0.0, s = 0.0;
+#pragma unroll 4
+            for (int j = lane; j < d; j += 64) {
+                sx = __dadd_rn(sx, (double)X[b * d + j]);
+                sy = __dadd_rn(sy, (double)Y[(int64_t)a * d + j]);
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                sx = __dadd_rn(sx, __shfl_xor(sx, off));
+                sy = __dadd_rn(sy, __shfl_xor(sy, off));
+            }
+#pragma unroll 4
+            for (int j = lane; j < d; j += 64)
+                s = __dadd_rn(s, fabs(__dsub_rn((double)X[b * d + j] / sx,
+                                                (double)Y[(int64_t)a * d + j] / sy)));
+            for (int off = 32; off > 0; off >>= 1) s = __dadd_rn(s, __shfl_xor(s, off));
+            if (lane != 0) continue;
+            if (k) ks += k8 ? reinterpret_cast<const uint8_t *>(k)[b * ldk + a] : k[b * ldk + a];
+            cs = __dadd_rn(cs, 0.5 * s);
+        }
+    }
+    for (int64_t b = lo + threadIdx.x; b < (cost_kind == 4 ? lo : hi); b += kFinalizeThreads) {
         const int32_t a = mate_b[b];
         if (a < 0) continue;
         if (k) {
@@ -1614,17 +1642,6 @@ finalize_kernel(int64_t n, const int32_t *mate_b, const int16_t *k, int64_t ldk,
                 s = __dadd_rn(s, __dmul_rn(t, t));
             }
             cs = __dadd_rn(cs, cost_kind == 3 ? sqrt(s) : s);
-        } else if (cost_kind == 4) {
-            // half the L1 distance of the vectors normalised to sum 1
-            double sx = 0.0, sy = 0.0, s = 0.0;
-            for (int j = 0; j < d; ++j) {
-                sx = __dadd_rn(sx, (double)X[b * d + j]);
-                sy = __dadd_rn(sy, (double)Y[(int64_t)a * d + j]);
-            }
-            for (int j = 0; j < d; ++j)
-                s = __dadd_rn(s, fabs(__dsub_rn((double)X[b * d + j] / sx,
-                                                (double)Y[(int64_t)a * d + j] / sy)));
-            cs = __dadd_rn(cs, 0.5 * s);
         }
     }
     sk[threadIdx.x] = ks;
