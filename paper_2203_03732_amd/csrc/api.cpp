@@ -65,6 +65,8 @@ struct prot_ctx {
         prot::OtInfo ot;
     } *stage = nullptr;              // pinned host memory
 
+    uint32_t *solo_lists = nullptr;  // candidate lists of the one-workgroup solver
+    bool loop_knobs = false;         // a PROT_LOOP_* variable asks for the loop as it sets it
     int64_t *rtime = nullptr;        // round timer (PROT_DEBUG_ROUND_TIMES=1)
     int32_t cost_path = PROT_COST_AUTO;    // prot_set_cost_path
     int32_t cost_metric = PROT_METRIC_SQEUCLIDEAN;  // prot_set_cost_metric
@@ -224,6 +226,9 @@ int ensure_loop(prot_ctx *c, int64_t n)
     if ((rc = dev_alloc(c, &c->t, (size_t)round_up(cap, 8)))) return rc;
     if ((rc = dev_alloc(c, &c->lists, (size_t)cap * 2))) return rc;
     if ((rc = dev_alloc(c, &c->tlists, (size_t)cap * 4 * prot::kMaxGroups))) return rc;
+    if (!c->solo_lists &&
+        (rc = dev_alloc(c, &c->solo_lists, (size_t)prot::kSoloMaxN * prot::kSoloListCap)))
+        return rc;
     // list entries carry tags; fresh memory must not hold one by chance
     HIP_TRY(c, prot::launch_fill_u64(c->tlists, cap * 4 * prot::kMaxGroups, 0ull, c->stream));
     c->cap_n = cap;
@@ -592,12 +597,64 @@ int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk,
     // a relaunch after the gate admitted too few workgroups: that attempt ran
     // nothing, only its error bit goes
     if (cooperative) HIP_TRY(c, prot::launch_clear_err(c->ctl, c->stream, 16));
+    const int32_t complete = (o && o->no_completion) ? 0 : 1;
+    hipEvent_t *le = nullptr;
+    // The one-workgroup solver (columns, costs and state as its LDS and its
+    // 16-bit arithmetic take them; a new start, whose duals are feasible): a
+    // phase there is two or three workgroup barriers and short lists, 2.4 to
+    // 5 us, against ~6.5 us of a grid's round barriers. It is slower while
+    // many rows look, each reading its whole row on one compute unit.
+    // - From the start where the matrix is small: 400 x 400 and 2 phases
+    //   95 -> 90 us, 17 202 -> 145, 231 1749 -> 730; 300 x 517 97 -> 70; but
+    //   512 x 512, 64 dimensions 169 -> 198.
+    // - Else it takes over once at most kSoloFewRows rows are free, if a good
+    //   part of the phases is still to come then: their number grows with
+    //   free / T, the change costs 10 to 15 us (n = 1,024: T = 51 313 -> 262 us,
+    //   T = 102, d = 64 175 -> 183), a whole row of more than 1,024 columns
+    //   twice as long (n = 2,048: T = 20 474 -> 383 us, T = 102 196 -> 222), and
+    //   rows that have spare columns are soon done (512 x 1,500: 5 phases, 123 -> 156).
+    const bool solo_cold = n * n_a <= prot::kSoloColdCells;
+    const bool solo_tail = n_a <= 1024 ? 2 * T <= prot::kSoloFewRows
+                                       : 4 * T <= prot::kSoloFewRows && 8 * (n_a - n) <= n_a;
+    const bool solo = n_a <= prot::kSoloMaxN && K <= prot::kSoloMaxK && !warm && !otf.d &&
+                      !cp.rmap && !cooperative && !c->loop_knobs && !c->rtime &&
+                      (solo_cold || solo_tail);
+    if (solo) {
+        prot::SoloArgs so{};
+        so.k = k;
+        so.ldk = ldk;
+        so.n_b = (int32_t)n;
+        so.n_a = (int32_t)n_a;
+        so.T = T;
+        so.origin = a.origin;
+        so.complete = complete;
+        so.cold = solo_cold ? 1 : 0;
+        so.k8 = k8;
+        so.max_phases = a.max_phases;
+        so.phase_bound = a.phase_bound;
+        so.lists = c->solo_lists;
+        so.ctl = c->ctl;
+        so.trace = a.trace;
+        so.mate_a = mate_a;
+        so.mate_b = mate_b;
+        so.y_a = y_a;
+        so.y_b = y_b;
+        if (!so.cold) {
+            a.few_rows = prot::kSoloFewRows;
+            HIP_TRY(c, prot::launch_init(a, 0, mate_a, mate_b, y_a, c->stream));
+        }
+        if (int r = next_loop_events(c, &le)) return r;
+        if (!so.cold) {
+            HIP_TRY(c, prot::launch_loop(a, grid, c->stream, le[0], nullptr));
+            HIP_TRY(c, prot::launch_decode(a, mate_a, mate_b, y_a, c->stream));
+        }
+        HIP_TRY(c, prot::launch_solo(so, c->stream, so.cold ? le[0] : nullptr, le[1]));
+        return PROT_OK;
+    }
     HIP_TRY(c, prot::launch_init(a, warm, mate_a, mate_b, y_a, c->stream));
     if (c->rtime) HIP_TRY(c, prot::launch_clear_times(c->rtime, c->stream));
-    hipEvent_t *le = nullptr;
     if (int r = next_loop_events(c, &le)) return r;
     HIP_TRY(c, prot::launch_loop(a, grid, c->stream, le[0], le[1]));
-    const int32_t complete = (o && o->no_completion) ? 0 : 1;
     HIP_TRY(c, prot::launch_finish(a, warm, complete, mate_a, mate_b, y_a, c->lists, c->stream));
     return PROT_OK;
 }
@@ -1030,6 +1087,10 @@ int prot_ctx_create(prot_ctx **out, int device, void *hip_stream)
                        : std::strcmp(v, "direct") == 0 ? PROT_COST_DIRECT
                                                        : PROT_COST_AUTO;
     if (const char *v = std::getenv("PROT_PRUNE_MIN_N")) c->prune_min_n = std::atoll(v);
+    for (const char *name : {"PROT_LOOP_GATE_CAP", "PROT_LOOP_COOPERATIVE",
+                             "PROT_LOOP_BARRIER_TICKS", "PROT_LOOP_GROUPS", "PROT_LOOP_WGS_PER_CU",
+                             "PROT_LOOP_MAX_GRID", "PROT_LOOP_T_GLOBAL", "PROT_LOOP_WIDE_ROWS"})
+        c->loop_knobs = c->loop_knobs || std::getenv(name) != nullptr;
     if (const char *v = std::getenv("PROT_LOOP_GATE_CAP")) c->gate_cap = std::max(0, std::atoi(v));
     if (const char *v = std::getenv("PROT_LOOP_COOPERATIVE")) c->cooperative = std::atoi(v) == 1;
     if (const char *v = std::getenv("PROT_LOOP_BARRIER_TICKS"))
@@ -1076,6 +1137,7 @@ int prot_ctx_destroy(prot_ctx *c)
     (void)hipFree(c->kmat);
     (void)hipFree(c->tpriv);
     (void)hipFree(c->th);
+    (void)hipFree(c->solo_lists);
     (void)hipFree(c->rtime);
     (void)hipFree(c->mfma_buf);
     (void)hipFree(c->l1_buf);

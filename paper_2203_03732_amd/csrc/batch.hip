@@ -11,17 +11,20 @@
 // The kernel does not need co-resident workgroups, so it can be captured in
 // a HIP graph and replayed.
 //
+// The same loop solves a single instance of few columns, or its last phases
+// (solo_kernel).
+//
 // Candidate lists. A free row looks for the first column with
 // v = k + t(a) = y(b) - 1 =: need. Its v never fall (t only grows) and need
 // never falls (y(b) only grows), so a list of all columns with v < V, taken
 // at any time, holds every column the row can find while need < V. Each row
-// keeps such a list of at most kListCap entries (column, k) with its V, and
+// keeps such a list of at most CAP entries (column, k) with its V, and
 // minv, a bound below which it can find nothing: most rows of a phase are
 // settled by minv alone (LDS) or by one 128-byte list, read by 8 lanes,
 // instead of their 2n bytes of the matrix. A row whose need has passed V
 // reads its whole row once (one wave, every chunk in flight), which finds its
-// column and writes the next list, with V as high as kListCap allows. A row
-// with more than kListCap columns at v = need gets no list and is read whole
+// column and writes the next list, with V as high as CAP allows. A row
+// with more than CAP columns at v = need gets no list and is read whole
 // whenever it is scanned.
 //
 // Bound: at first instruction issue (every row is read whole once and its list
@@ -39,8 +42,6 @@
 namespace prot {
 namespace {
 
-constexpr int kListCap = kBatchListCap;  // entries of a row's candidate list
-constexpr int kListLanes = kListCap / 4; // lanes that read one list (16 bytes each)
 constexpr uint32_t kListFill = 0x7FFF0000u;  // column 0 with a k that never matches
 constexpr uint16_t kNone16 = 0xFFFF;
 constexpr int32_t kBatchWideMax = 256;
@@ -57,7 +58,8 @@ __device__ inline uint32_t batch_key(uint32_t r, int b)
     return (r << kKeyRowBits) | (kKeyRowMask - (uint32_t)b);
 }
 
-template <int NMAX, int NT>
+// CAP: entries of a row's candidate list, read by CAP / 4 lanes (16 bytes each).
+template <int NMAX, int NT, int CAP>
 struct BatchShared {
     alignas(16) uint32_t key[NMAX];
     alignas(16) uint16_t t[NMAX];  // -y(a)
@@ -74,12 +76,13 @@ struct BatchShared {
     // smallest k + t it has
     uint16_t pa[NMAX];
     uint16_t pm[NMAX];
-    alignas(16) uint32_t stage[NT / 64][kListCap];  // a wave's list on its way to memory
+    alignas(16) uint32_t stage[NT / 64][CAP];  // a wave's list on its way to memory
     uint32_t wcnt[16];
     long long red_k[16];
     double red_c[16];
     unsigned long long red_s[16];
     uint32_t nF[2], nl[2], nd[2], prop[2];
+    uint32_t tr_scan[2], tr_none[2];  // per-phase record: entries examined, rows that found none
     int32_t job;
 };
 
@@ -119,20 +122,36 @@ __device__ inline uint32_t pairs_above(uint32_t v, uint32_t D, uint32_t one)
 // pairs_above(word w) << 2w.
 __device__ inline uint32_t low_bits(uint32_t x) { return ~(x | (x >> 15)) & 0xFFu; }
 
+// The rounded costs of columns col0 .. col0 + 7 of a row. A matrix of bytes
+// (kBytes) holds padding as 0xFF, which becomes the 0x7FFF of a 16-bit one.
+template <bool kBytes>
+__device__ inline uint4 load_8(const int16_t *__restrict__ k, int64_t at)
+{
+    if constexpr (!kBytes) return *reinterpret_cast<const uint4 *>(k + at);
+    const uint2 v = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint8_t *>(k) + at);
+    auto widen = [](uint32_t w, uint32_t sel) {
+        const u16x2 p = as_pair(__builtin_amdgcn_perm(0u, w, sel));
+        return as_word(p | (((p + (u16x2)(uint16_t)1) >> (u16x2)(uint16_t)8) *
+                            (u16x2)(uint16_t)0x7F00));
+    };
+    return make_uint4(widen(v.x, 0x0C010C00u), widen(v.x, 0x0C030C02u), widen(v.y, 0x0C010C00u),
+                      widen(v.y, 0x0C030C02u));
+}
+
 // A whole row held by one wave: chunk c is columns 512 c + 8 lane .. + 7.
 template <int NC>
 struct RowRegs {
     uint4 c[NC];
 };
-template <int NC>
-__device__ inline RowRegs<NC> load_row(const int16_t *__restrict__ row, int n, int lane)
+template <int NC, bool kBytes>
+__device__ RowRegs<NC> load_row(const int16_t *__restrict__ k, int64_t row, int n, int lane)
 {
     RowRegs<NC> r;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const int col0 = c * 512 + lane * 8;
         r.c[c] = make_uint4(0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu, 0x7FFF7FFFu);
-        if (col0 < n) r.c[c] = *reinterpret_cast<const uint4 *>(row + col0);
+        if (col0 < n) r.c[c] = load_8<kBytes>(k, row + col0);
     }
     return r;
 }
@@ -166,7 +185,7 @@ struct SelectWord<1> {
 // k: the row; S_t: the duals in LDS.
 // Bound: instruction issue (about 3 instructions per 2 columns and pass over
 // the row: the sums and their minimum, then one or two list masks).
-template <int NC>
+template <int NC, int kListCap>
 __device__ Hit direct_row(const RowRegs<NC> &k, const uint16_t *S_t, int n,
                           int origin, int need, int lane, uint32_t *stage, uint16_t *minv,
                           uint16_t *V, int *window)
@@ -270,67 +289,109 @@ __device__ Hit direct_row(const RowRegs<NC> &k, const uint16_t *S_t, int n,
         const uint32_t v = ((i & 1) ? pair >> 16 : pair & 0xFFFFu) + (uint32_t)need;
         stage[at++] = (uint32_t)col | ((v - S_t[col]) << 16);
     }
-    if (lane >= cnt && lane < kListCap) stage[lane] = kListFill;
+#pragma unroll
+    for (int i = 0; i < kListCap; i += 64)
+        if (i + lane >= cnt && i + lane < kListCap) stage[i + lane] = kListFill;
     return h;
 }
 
-template <int NMAX, int NT>
-__device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, NT> &S, bool timed)
+// An instance: nb rows, na >= nb columns.
+struct LdsJob {
+    int nb, na;
+    const int16_t *k;  // or bytes (kBytes)
+    int64_t ldk;
+    uint32_t *lists;
+    int64_t T, max_phases, bound;
+    int origin;
+    int64_t *trace, *rtime;  // may be null
+};
+// Its totals, and where its free rows are (S.F[cur]).
+struct LdsRun {
+    int64_t phases, sum_free, rounds, max_rounds;
+    unsigned long long scanned;  // this thread's share
+    int status;                  // 0, 1 stopped at max_phases, 2 by the bound
+    int cur;
+};
+
+// Initial state (Section 2.2): y(b) = 1, y(a) = 0, M empty.
+template <int NMAX, int NT, int CAP>
+__device__ void lds_cold(const LdsJob &J, BatchShared<NMAX, NT, CAP> &S)
+{
+    for (int i = threadIdx.x; i < ((J.na + 7) & ~7); i += NT) S.t[i] = 0;
+    for (int i = threadIdx.x; i < J.na; i += NT) S.mate[i] = kNone16;
+    for (int i = threadIdx.x; i < J.nb; i += NT) {
+        S.y[i] = 1;
+        S.F[0][i] = (uint16_t)i;
+    }
+    if (threadIdx.x == 0) S.nF[0] = (uint32_t)J.nb;
+}
+
+// The phases from the state in S (t, mate, y, F[0] and nF[0], set by any
+// thread) until at most T rows are free. kTrace: record each phase.
+template <int NMAX, int NT, int CAP, bool kTrace, bool kBytes = false>
+__device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP> &S)
 {
     constexpr int NC = NMAX / 512;
     constexpr int kWaves = NT / 64;
+    constexpr int kListCap = CAP, kListLanes = CAP / 4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = A.n_arr[inst];
-    const int64_t off = A.pt_off[inst];
-    const int16_t *k = A.k + A.k_off[inst];
-    const int64_t ldk = A.ldk_arr[inst];
-    uint32_t *lists = A.lists + off * kListCap;
-    const int64_t T = (int64_t)floor(A.eps * (double)n + 1e-9);
-    // the watchdog: a cold start needs at most (2n(K + 2) - n) / (T + 1)
-    // phases (Lemma 3.2 with eq. (4)); more means a fault
-    const int64_t bound =
-        A.phase_bound ? A.phase_bound
-                      : (2 * (int64_t)n * ((int64_t)floor(1.0 / A.eps) + 2) - n) / (T + 1);
-
-    // Initial state (Section 2.2): y(b) = 1, y(a) = 0, M empty; no lists
-    // (V = 0) and nothing known (minv = 0 makes every row look).
-    for (int i = tid; i < ((n + 7) & ~7); i += NT) S.t[i] = 0;
+    const int n = J.na;
+    const int16_t *k = J.k;
+    const int64_t ldk = J.ldk;
+    uint32_t *lists = J.lists;
+    const bool timed = J.rtime != nullptr;
+    // no lists (V = 0) and nothing known (minv = 0 makes every row look)
     for (int i = tid; i < n; i += NT) {
         S.key[i] = 0u;
-        S.mate[i] = kNone16;
-        S.y[i] = 1;
-        S.F[0][i] = (uint16_t)i;
         S.minv[i] = 0;
         S.V[i] = 0;
     }
     if (tid == 0) {
-        S.nF[0] = (uint32_t)n;
         S.nF[1] = 0;
         S.nl[0] = S.nl[1] = S.nd[0] = S.nd[1] = S.prop[0] = S.prop[1] = 0;
+        S.tr_scan[0] = S.tr_scan[1] = S.tr_none[0] = S.tr_none[1] = 0;
     }
-    int64_t phases = 0, sum_free = 0, rounds = 0, max_rounds = 0;
+    int64_t phases = R.phases, sum_free = 0, rounds = 0, max_rounds = R.max_rounds;
     unsigned long long scanned = 0;  // this thread's share
+    // the last finished phase's record, written by thread 0 once every wave
+    // has passed a barrier after adding to it
+    int64_t traced = -1;
+    uint32_t tr_free = 0;
+    int64_t tr_rounds = 0;
+    auto write_trace = [&]() {
+        if (traced < 0 || tid != 0) return;
+        const int e = (int)(traced & 1);
+        if (J.trace && traced < kTraceCap) {
+            int64_t *t = J.trace + 4 * traced;
+            t[0] = tr_free;
+            t[1] = tr_rounds;
+            t[2] = S.tr_scan[e];
+            t[3] = (int64_t)tr_free - S.tr_none[e];
+        }
+        S.tr_scan[e] = S.tr_none[e] = 0;
+        traced = -1;
+    };
     uint32_t r = 0;
     int cur = 0, q = 0;
-    int status = 0;
+    int status = R.status;
     int window = 4;      // of this wave's last list (direct_row)
     bool quick = true;   // this wave looks at 512 columns before a whole row
     uint32_t block = 8;
     __syncthreads();
     for (;;) {
         const uint32_t nF = S.nF[cur];
-        if ((int64_t)nF <= T) break;
-        if (A.max_phases > 0 && phases >= A.max_phases) {
+        if ((int64_t)nF <= J.T || status != 0) break;
+        if (J.max_phases > 0 && phases >= J.max_phases) {
             status = 1;
             break;
         }
-        if (bound > 0 && phases >= bound) {
-            status = -4;
-            if (tid == 0)
-                __hip_atomic_fetch_or(A.err, 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (J.bound > 0 && phases >= J.bound) {
+            status = 2;
             break;
         }
+        const unsigned long long scanned_before = scanned;
+        uint32_t none = 0;  // rows of this wave that found no column
         phases += 1;
         sum_free += nF;
         const int nx = cur ^ 1;
@@ -351,6 +412,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                 listed = !skip && need < (int)S.V[b];
             }
             const uint32_t f = wave_push(&S.nF[nx], skip);
+            if (kTrace) none += (uint32_t)__popcll(__ballot(skip));
             const uint32_t l = wave_push(&S.nl[q], listed);
             const uint32_t dd = wave_push(&S.nd[q], in && !skip && !listed);
             if (skip) {
@@ -364,6 +426,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
             }
         }
         __syncthreads();
+        if (kTrace) write_trace();
         int64_t phase_rounds = 0;
         for (;;) {
             r += 1;
@@ -389,14 +452,14 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                 auto slot = [&](int e) { return NMAX - 1 - (int)i0 - e * kWaves; };
                 if (quick) {
                     auto start_of = [&](int b, int pos) {
-                        int c = (A.origin == 0 ? b : 0) + pos;
+                        int c = (J.origin == 0 ? b : 0) + pos;
                         return c >= n ? c - n : c;
                     };
                     auto load_window = [&](int e, int *b, int *c) {
                         *b = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(e)]);
                         *c = start_of(*b, __builtin_amdgcn_readfirstlane((int)S.ap[q][slot(e)]));
                         const int col0 = (*c & ~7) + lane * 8;
-                        return col0 < n ? *reinterpret_cast<const uint4 *>(k + (int64_t)*b * ldk + col0)
+                        return col0 < n ? load_8<kBytes>(k, (int64_t)*b * ldk + col0)
                                         : make_uint4(~0u, ~0u, ~0u, ~0u);
                     };
                     int bn, cn;
@@ -409,7 +472,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                         const int col0 = (c & ~7) + lane * 8;
                         // a scan that started at origin + pos wraps at n and ends
                         // before its origin
-                        const int origin = A.origin == 0 ? b : 0;
+                        const int origin = J.origin == 0 ? b : 0;
                         const int end = c < origin ? origin : n;
                         uint32_t m = 0;
                         if (col0 < end)
@@ -436,7 +499,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                 int en = __builtin_ctzll(left), overflowed = 0;
                 const int full = __builtin_popcountll(left);
                 int bn = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(en)]);
-                RowRegs<NC> kn = load_row<NC>(k + (int64_t)bn * ldk, n, lane);
+                RowRegs<NC> kn = load_row<NC, kBytes>(k, (int64_t)bn * ldk, n, lane);
                 // A row's list is stored while the next row is looked at,
                 // before the loads of the row after that: the wait for those
                 // loads then does not wait for a store just issued.
@@ -454,13 +517,13 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                     if (left) {
                         en = __builtin_ctzll(left);
                         bn = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(en)]);
-                        kn = load_row<NC>(k + (int64_t)bn * ldk, n, lane);
+                        kn = load_row<NC, kBytes>(k, (int64_t)bn * ldk, n, lane);
                     }
                     const int need = __builtin_amdgcn_readfirstlane((int)S.y[b] - 1);
                     const int pos = S.ap[q][at];
-                    const int origin = A.origin == 0 ? b : 0;
+                    const int origin = J.origin == 0 ? b : 0;
                     uint16_t minv, V;
-                    const Hit h = direct_row<NC>(kr, S.t, n, origin, need, lane, S.stage[wave],
+                    const Hit h = direct_row<NC, CAP>(kr, S.t, n, origin, need, lane, S.stage[wave],
                                                  &minv, &V, &window);
                     stored = V ? b : -1;
                     overflowed += V == 0;
@@ -492,7 +555,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                         lists + (int64_t)b * kListCap + (lane % kListLanes) * 4);
                     need = (int)S.y[b] - 1;
                     pos = S.ap[q][i];
-                    origin = A.origin == 0 ? b : 0;
+                    origin = J.origin == 0 ? b : 0;
                     const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -503,8 +566,8 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                         lo = min(lo, v);
                     }
                 }
-                j = group8_min_u32(j);
-                lo = group8_min_u32(lo);
+                j = group_min_u32<kListLanes>(j);
+                lo = group_min_u32<kListLanes>(lo);
                 if (!in || lane % kListLanes != 0) continue;
                 if (j != 0x7FFFFFFFu) {
                     const int a = origin + (int)j < n ? origin + (int)j : origin + (int)j - n;
@@ -522,10 +585,10 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
             // (the lists written are read after the next barrier at the earliest)
             barrier_lds();
             if (timed && tid == 0 && 4u * r <= 3u * (uint32_t)kRoundTimeCap) {
-                A.rtime[4 * (r - 1)] = t_start;
-                A.rtime[4 * (r - 1) + 1] = (int64_t)wall_clock64();
-                A.rtime[4 * (r - 1) + 2] = nl + nd;
-                A.rtime[4 * (r - 1) + 3] = phases;
+                J.rtime[4 * (r - 1)] = t_start;
+                J.rtime[4 * (r - 1) + 1] = (int64_t)wall_clock64();
+                J.rtime[4 * (r - 1) + 2] = nl + nd;
+                J.rtime[4 * (r - 1) + 3] = phases;
             }
             if (S.prop[q]) phase_rounds += 1;
             // Winners: step (II), the column's old mate is free in the next
@@ -561,6 +624,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                         S.minv[b] = S.pm[at];
                     }
                 }
+                if (kTrace) none += (uint32_t)__popcll(__ballot(i < top && a == kNone16));
                 const uint32_t f = wave_push(&S.nF[nx], freed != kNone16);
                 const uint32_t l = wave_push(&S.nl[q ^ 1], listed);
                 const uint32_t dd = wave_push(&S.nd[q ^ 1], lost && !listed);
@@ -578,19 +642,46 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
         rounds += phase_rounds;
         if (phase_rounds > max_rounds) max_rounds = phase_rounds;
         cur = nx;
+        if (kTrace) {
+            const uint32_t sc = wave_sum_u32((uint32_t)(scanned - scanned_before));
+            if (lane == 0) {
+                if (sc) atomicAdd(&S.tr_scan[(phases - 1) & 1], sc);
+                if (none) atomicAdd(&S.tr_none[(phases - 1) & 1], none);
+            }
+            traced = phases - 1;
+            tr_free = nF;
+            tr_rounds = phase_rounds;
+        }
     }
-    const uint32_t nfree = S.nF[cur];
+    if (kTrace) {
+        __syncthreads();
+        write_trace();
+    }
+    R.phases = phases;
+    R.sum_free += sum_free;
+    R.rounds += rounds;
+    R.max_rounds = max_rounds;
+    R.scanned += scanned;
+    R.status = status;
+    R.cur = cur;
+}
 
-    // Matching from the mates; the free rows are F[cur], the free columns the
-    // never-taken ones. Completion (Section 2.1): i-th free b (ascending)
-    // with the i-th free a (ascending).
+// The matching from the mates: mb = S.ap[0], ma = S.ap[1] (kNone16: free; the
+// free rows are F[cur], the free columns the never-taken ones). complete
+// (Section 2.1): i-th free b (ascending) with the i-th free a (ascending).
+template <int NMAX, int NT, int CAP>
+__device__ void lds_matching(const LdsJob &J, int cur, bool complete, BatchShared<NMAX, NT, CAP> &S)
+{
+    constexpr int kWaves = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t nfree = S.nF[cur];
     uint16_t *mb = S.ap[0], *ma = S.ap[1];
-    for (int i = tid; i < n; i += NT) {
+    for (int i = tid; i < J.nb; i += NT) {
         mb[i] = kNone16;
         S.pa[i] = 0;
     }
     __syncthreads();
-    for (int i = tid; i < n; i += NT) {
+    for (int i = tid; i < J.na; i += NT) {
         const uint16_t b = S.mate[i];
         ma[i] = b;
         if (b != kNone16) mb[b] = (uint16_t)i;
@@ -598,7 +689,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
     for (uint32_t i = tid; i < nfree; i += NT) S.pa[S.F[cur][i]] = 1;
     __syncthreads();
     // ascending list of the i < n with flag(i), by all threads
-    auto ordered_list = [&](auto flag, uint16_t *out) {
+    auto ordered_list = [&](int n, auto flag, uint16_t *out) {
         int base = 0;
         for (int i0 = 0; i0 < n; i0 += NT) {
             const bool f = i0 + tid < n && flag(i0 + tid);
@@ -616,16 +707,44 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
         }
         return base;
     };
-    if (A.complete && status >= 0) {
-        const int nb = ordered_list([&](int i) { return S.pa[i] != 0; }, S.ab[0]);
-        const int na = ordered_list([&](int i) { return S.mate[i] == kNone16; }, S.ab[1]);
-        const int m = min(nb, na);
-        for (int i = tid; i < m; i += NT) {
-            mb[S.ab[0][i]] = S.ab[1][i];
-            ma[S.ab[1][i]] = S.ab[0][i];
-        }
-        __syncthreads();
+    if (!complete) return;
+    const int nb = ordered_list(J.nb, [&](int i) { return S.pa[i] != 0; }, S.ab[0]);
+    const int na = ordered_list(J.na, [&](int i) { return S.mate[i] == kNone16; }, S.ab[1]);
+    const int m = min(nb, na);
+    for (int i = tid; i < m; i += NT) {
+        mb[S.ab[0][i]] = S.ab[1][i];
+        ma[S.ab[1][i]] = S.ab[0][i];
     }
+    __syncthreads();
+}
+
+template <int NMAX, int NT, int CAP>
+__device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, NT, CAP> &S, bool timed)
+{
+    constexpr int kWaves = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = A.n_arr[inst];
+    const int64_t off = A.pt_off[inst];
+    const int16_t *k = A.k + A.k_off[inst];
+    const int64_t ldk = A.ldk_arr[inst];
+    const int64_t T = (int64_t)floor(A.eps * (double)n + 1e-9);
+    // the watchdog: a cold start needs at most (2n(K + 2) - n) / (T + 1)
+    // phases (Lemma 3.2 with eq. (4)); more means a fault
+    const int64_t bound =
+        A.phase_bound ? A.phase_bound
+                      : (2 * (int64_t)n * ((int64_t)floor(1.0 / A.eps) + 2) - n) / (T + 1);
+    const LdsJob J{n, n, k, ldk, A.lists + off * CAP, T, A.max_phases, bound, A.origin,
+                   nullptr, timed ? A.rtime : nullptr};
+    LdsRun R{};
+    lds_cold(J, S);
+    lds_phases<NMAX, NT, CAP, false>(J, R, S);
+    unsigned long long scanned = R.scanned;
+    const int status = R.status == 2 ? -4 : R.status;
+    if (R.status == 2 && tid == 0)
+        __hip_atomic_fetch_or(A.err, 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t nfree = S.nF[R.cur];
+    lds_matching(J, R.cur, A.complete && status >= 0, S);
+    const uint16_t *mb = S.ap[0], *ma = S.ap[1];
 
     // Outputs and per-instance statistics (fixed-order reductions).
     const float *X = A.X + off * A.d, *Y = A.Y + off * A.d;
@@ -666,10 +785,10 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
         }
         InstanceStats &st = A.stats[inst];
         const float m = A.m[inst];
-        st.phases = phases;
-        st.sum_free = sum_free;
-        st.rounds = rounds;
-        st.max_rounds = max_rounds;
+        st.phases = R.phases;
+        st.sum_free = R.sum_free;
+        st.rounds = R.rounds;
+        st.max_rounds = R.max_rounds;
         st.scanned = (int64_t)scanned;
         st.matched_in_phases = n - (int64_t)nfree;
         st.completed_pairs = A.complete ? (int64_t)nfree : 0;
@@ -687,7 +806,7 @@ template <int NMAX, int NT>
 // (4 waves per SIMD: two workgroups of 512 threads or one of 1,024 a CU)
 __global__ void __launch_bounds__(NT, 4) batch_solve_kernel(BatchArgs A)
 {
-    __shared__ BatchShared<NMAX, NT> S;
+    __shared__ BatchShared<NMAX, NT, kBatchListCap> S;
     for (;;) {
         if (threadIdx.x == 0)
             S.job = (int32_t)__hip_atomic_fetch_add(A.queue, 1u, __ATOMIC_RELAXED,
@@ -696,7 +815,91 @@ __global__ void __launch_bounds__(NT, 4) batch_solve_kernel(BatchArgs A)
         const int job = S.job;
         __syncthreads();
         if (job >= A.batch) break;
-        solve_instance<NMAX, NT>(A, A.order[job], S, A.rtime != nullptr && job == 0);
+        solve_instance<NMAX, NT, kBatchListCap>(A, A.order[job], S, A.rtime != nullptr && job == 0);
+    }
+}
+
+// One instance, from the start (cold) or from the state that a phase loop of
+// many workgroups left in the outputs once few rows were free. The outputs,
+// the completion and the control block are those of the kernels that follow
+// the loop.
+// Bound: latency, three workgroup barriers and two dependent LDS or list
+// reads a phase, ~2.5 us more where a row is read whole. Euclidean cost,
+// d = 2, eps = 0.01, whole solves: n = 300 (1,259 phases) 8.4 -> 3.4 ms, 1,024
+// (1,416) 9.4 -> 5.2, 2,048 (1,528) 10.7 -> 7.6; with lists of 32 entries 3.8,
+// 5.4 and 8.0, of 128 3.2, 5.0 and 7.7 but squared costs 3 to 5 % slower.
+template <int NMAX, int NT, int CAP, bool kBytes>
+__global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
+{
+    __shared__ BatchShared<NMAX, NT, CAP> S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    Ctl *c = A.ctl;
+    const LdsJob J{A.n_b, A.n_a, A.k, A.ldk, A.lists, A.T, A.max_phases, A.phase_bound, A.origin,
+                   A.trace, nullptr};
+    const int32_t err = c->err;
+    LdsRun R{};
+    if (A.cold) {
+        lds_cold(J, S);
+        if (A.trace && tid < 4) A.trace[tid] = 0;
+    } else {
+        if (err & kErrLoop) {
+            // the loop failed: the outputs are marked invalid (every vertex
+            // free); the host reports the error
+            for (int i = tid; i < A.n_b; i += NT) A.mate_b[i] = -1;
+            for (int i = tid; i < A.n_a; i += NT) A.mate_a[i] = -1;
+            return;
+        }
+        if (err & 16) return;  // (nothing ran)
+        R.phases = c->phases;
+        R.sum_free = c->sum_free;
+        R.rounds = c->rounds;
+        R.max_rounds = c->max_rounds;
+        R.scanned = tid == 0 ? c->scanned : 0ull;
+        R.status = c->status;
+        if (tid == 0) S.nF[0] = 0;
+        __syncthreads();
+        for (int i = tid; i < ((A.n_a + 7) & ~7); i += NT)
+            S.t[i] = i < A.n_a ? (uint16_t)-A.y_a[i] : 0;
+        for (int i = tid; i < A.n_a; i += NT) {
+            const int32_t m = A.mate_a[i];
+            S.mate[i] = m >= 0 ? (uint16_t)m : kNone16;
+        }
+        for (int i0 = wave * 64; i0 < A.n_b; i0 += NT) {
+            const int i = i0 + lane;
+            const bool is_free = i < A.n_b && A.mate_b[i] < 0;
+            if (i < A.n_b) S.y[i] = (uint16_t)A.y_b[i];
+            const uint32_t f = wave_push(&S.nF[0], is_free);
+            if (is_free) S.F[0][f] = (uint16_t)i;
+        }
+    }
+    lds_phases<NMAX, NT, CAP, true, kBytes>(J, R, S);
+    // (a solve stopped early keeps its state, without the completion)
+    lds_matching(J, R.cur, A.complete && R.status == 0 && err == 0, S);
+    const uint32_t nfree = S.nF[R.cur];
+    for (int i = tid; i < A.n_a; i += NT) {
+        const uint16_t m = S.ap[1][i];
+        A.mate_a[i] = m == kNone16 ? -1 : (int)m;
+        A.y_a[i] = -(int32_t)S.t[i];
+    }
+    for (int i = tid; i < A.n_b; i += NT) {
+        const uint16_t m = S.ap[0][i];
+        A.mate_b[i] = m == kNone16 ? -1 : (int)m;
+        A.y_b[i] = S.y[i];
+    }
+    unsigned long long scanned = R.scanned;
+    for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o);
+    if (lane == 0) S.red_s[wave] = scanned;
+    __syncthreads();
+    if (tid == 0) {
+        scanned = 0;
+        for (int w = 0; w < NT / 64; ++w) scanned += S.red_s[w];
+        c->scanned = scanned;
+        c->status = R.status;
+        c->phases = R.phases;
+        c->sum_free = R.sum_free;
+        c->rounds = R.rounds;
+        c->max_rounds = R.max_rounds;
+        c->free_after = nfree;
     }
 }
 
@@ -714,6 +917,18 @@ auto with_batch_kernel(int32_t n_max, int32_t batch, F f)
 }  // namespace
 
 int32_t batch_max_n() { return 2048; }
+
+hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    SoloArgs copy = a;
+    void *args[] = {&copy};
+    const void *fn =
+        a.n_a > 1024 ? (a.k8 ? (const void *)solo_kernel<2048, 1024, kSoloListCap, true>
+                             : (const void *)solo_kernel<2048, 1024, kSoloListCap, false>)
+                     : (a.k8 ? (const void *)solo_kernel<1024, 1024, kSoloListCap, true>
+                             : (const void *)solo_kernel<1024, 1024, kSoloListCap, false>);
+    return hipExtLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s, ev_start, ev_stop, 0);
+}
 
 hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid)
 {

@@ -87,7 +87,8 @@ __device__ inline uint32_t dpp_u32(uint32_t identity, uint32_t v)
 }
 constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141,
+              kDppMirror = 0x140;
 
 // lane i: v(0) + ... + v(i)
 __device__ inline uint32_t wave_inclusive_sum_u32(uint32_t v)
@@ -114,12 +115,16 @@ __device__ inline uint32_t wave_min_u32(uint32_t v)
     v = min(v, dpp_u32<kDppBcast31, 0xC>(0xFFFFFFFFu, v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
-// minimum over each group of 8 lanes, in all of them
-__device__ inline uint32_t group8_min_u32(uint32_t v)
+// minimum over each group of N = 8, 16 or 32 lanes, in all of them
+template <int N>
+__device__ inline uint32_t group_min_u32(uint32_t v)
 {
     v = min(v, dpp_u32<kDppXor1>(0xFFFFFFFFu, v));
     v = min(v, dpp_u32<kDppXor2>(0xFFFFFFFFu, v));
-    return min(v, dpp_u32<kDppHalfMirror>(0xFFFFFFFFu, v));
+    v = min(v, dpp_u32<kDppHalfMirror>(0xFFFFFFFFu, v));
+    if constexpr (N >= 16) v = min(v, dpp_u32<kDppMirror>(0xFFFFFFFFu, v));
+    if constexpr (N >= 32) v = min(v, (uint32_t)__shfl_xor((int)v, 16));
+    return v;
 }
 
 struct Hit {

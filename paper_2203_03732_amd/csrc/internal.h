@@ -127,6 +127,9 @@ struct LoopArgs {
     // Column duals in global memory (null: in LDS): each workgroup keeps its
     // copy of t in tpriv + blockIdx.x * n_pad, for columns beyond LDS.
     uint16_t *tpriv;
+    // leave at a phase start with at most this many free rows (0: never): the
+    // one-workgroup solver goes on from there
+    int64_t few_rows;
 };
 constexpr uint32_t kGateClosed = 0x80000000u;
 
@@ -215,6 +218,28 @@ hipError_t launch_points_mfma(const PointsJob &j, const MfmaAux &x, int64_t n_ma
 constexpr int kBatchListCap = 32;
 int32_t batch_max_n();
 hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid);
+// One instance solved by one workgroup (n_a <= kSoloMaxN), with its completion.
+constexpr int64_t kSoloMaxN = 2048;
+constexpr int64_t kSoloMaxK = 16000;        // 2 K + 2 stays below the padding's 0x7FFF
+constexpr int kSoloListCap = 64;            // entries of a row's candidate list
+constexpr int64_t kSoloColdCells = 160000;  // matrix entries it takes from the start
+constexpr int64_t kSoloFewRows = 128;       // free rows it takes over from the loop
+struct SoloArgs {
+    const int16_t *k;
+    int64_t ldk;
+    int32_t n_b, n_a;
+    int64_t T;
+    int32_t origin;
+    int32_t complete;
+    int32_t cold;             // 0: goes on from the outputs and the control block
+    int32_t k8;               // 1: k is a uint8 matrix
+    int64_t max_phases, phase_bound;  // as in LoopArgs
+    uint32_t *lists;          // kSoloListCap entries per row
+    Ctl *ctl;
+    int64_t *trace;
+    int32_t *mate_a, *mate_b, *y_a, *y_b;
+};
+hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipStream_t s);
 
 // loss.hip
@@ -254,6 +279,9 @@ hipError_t launch_loop_multi(const LoopArgs *arr, int count, int team, int32_t n
 hipError_t launch_team_finish(const TeamArgs &t, hipStream_t s);
 hipError_t launch_finish(const LoopArgs &a, int32_t warm, int32_t complete,
                          int32_t *mate_a, int32_t *mate_b, int32_t *y_a, int32_t *scratch,
+                         hipStream_t s);
+// The part of it before the completion (cold starts).
+hipError_t launch_decode(const LoopArgs &a, int32_t *mate_a, int32_t *mate_b, int32_t *y_a,
                          hipStream_t s);
 // cost_kind: 0 none, 1 cost matrix C (ldc), 2 points X, Y (d) with scale m.
 // With k == nullptr (points, costs on the fly) the rounded cost of each

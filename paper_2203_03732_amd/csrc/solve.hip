@@ -865,7 +865,7 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
         pend = 0;
     };
     for (;;) {
-        if ((int64_t)n_i <= A.T) break;
+        if ((int64_t)n_i <= A.T || (int64_t)n_i <= A.few_rows) break;
         if (A.max_phases > 0 && p >= A.max_phases) {
             if (leader) ctl->status = 1;
             break;
@@ -1965,6 +1965,14 @@ hipError_t launch_team_finish(const TeamArgs &t, hipStream_t s)
     if (t.batch > 0)
         hipLaunchKernelGGL(team_finish_kernel, dim3((unsigned)t.batch), dim3(kCompleteThreads), 0,
                            s, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_decode(const LoopArgs &a, int32_t *mate_a, int32_t *mate_b, int32_t *y_a,
+                         hipStream_t s)
+{
+    hipLaunchKernelGGL(decode_kernel, dim3(blocks_for(a.n_a, 256)), dim3(256), 0, s, a, mate_a,
+                       mate_b, y_a);
     return hipGetLastError();
 }
 
