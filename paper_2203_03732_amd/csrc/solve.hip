@@ -70,7 +70,7 @@ constexpr int64_t kBarrierTicks = 1000000000ll;
 constexpr int32_t kDualMax = 0x7FFF;           // t (-y(a)) fits its 15-bit field
 // Proposals are combined within a workgroup from this many rows still looking.
 constexpr uint32_t kCombineMin = 16;
-constexpr uint32_t kPublishMin = 128;   // workgroups from which barrier sums are published
+constexpr uint32_t kPublishMin = 256;   // workgroups from which barrier sums are published
 constexpr uint32_t kCombineSlots = 64;  // (768 bytes of LDS)
 constexpr int kGateSpin = 256;                 // gate polls (~0.3 ms) before it closes early
 
@@ -779,9 +779,10 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
     // words: a group's last arrival publishes its sum. Polling takes a word's
     // line to every XCD, and an arrival while others poll takes ~1.2 us
     // instead of ~0.6; but the sum is seen ~0.3 us later, so that few
-    // workgroups, which arrive together, poll the words (a solve of ~1,000
-    // rows, 63 workgroups: 3% faster so; the n = 10,000 Euclidean loop of 256
-    // workgroups 10.2 -> 9.8 ms by publishing).
+    // workgroups, which arrive together, poll the words (solves of
+    // ~1,000 and 2,104 rows, 63 and 132 workgroups: 3% faster so, of 4,000, 250
+    // workgroups, 2%; 4,200 and 5,000 rows, 256 workgroups: the same either
+    // way; the n = 10,000 Euclidean loop 10.2 -> 9.8 ms by publishing).
     const bool publish = !kMulti && nwg >= kPublishMin;
     const uint32_t xcd = kMulti ? 0u : xcd_id();
     const int grp = (int)(kMulti ? wg % (uint32_t)G
