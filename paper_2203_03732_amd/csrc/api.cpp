@@ -102,13 +102,13 @@ struct prot_ctx {
         double *rv = nullptr, *qv = nullptr, *R = nullptr, *Q = nullptr;
         prot::OtInfo *info = nullptr;
         // the copies kept as clusters (prot_ot_solve_clustered)
-        int64_t ccap_b = 0, ccap_a = 0, ccap_cells = 0, ccap_mask = 0;
+        int64_t ccap_b = 0, ccap_a = 0, ccap_cells = 0, ccap_stage = 0, ccap_mask = 0;
         int2 *cw = nullptr;
         unsigned long long *cmask = nullptr, *cmsum = nullptr;
         uint16_t *cstage = nullptr;
         int32_t *cY = nullptr, *cF = nullptr, *cZ = nullptr, *ctop = nullptr, *cbot = nullptr,
-                *cG = nullptr, *cact = nullptr, *cneed = nullptr, *czt = nullptr,
-                *cloff = nullptr, *cllen = nullptr;
+                *cG = nullptr, *czt = nullptr;
+        unsigned long long *cact = nullptr, *crowblk = nullptr;
         uint32_t *csync = nullptr;
         int64_t *cPF = nullptr, *cPG = nullptr;
     } ot;
@@ -1148,8 +1148,8 @@ int prot_ctx_destroy(prot_ctx *c)
                     (void *)c->ot.mate_a, (void *)c->ot.mate_b, (void *)c->ot.y_a,
                     (void *)c->ot.y_b, (void *)c->ot.rv, (void *)c->ot.qv, (void *)c->ot.R,
                     (void *)c->ot.Q, (void *)c->ot.info, (void *)c->ot.cw, (void *)c->ot.cmask, (void *)c->ot.cmsum,
-                    (void *)c->ot.cstage, (void *)c->ot.cact, (void *)c->ot.cneed,
-                    (void *)c->ot.czt, (void *)c->ot.cloff, (void *)c->ot.cllen,
+                    (void *)c->ot.cstage, (void *)c->ot.cact,
+                    (void *)c->ot.czt, (void *)c->ot.crowblk,
                     (void *)c->ot.csync, (void *)c->ot.cY, (void *)c->ot.cF, (void *)c->ot.cZ,
                     (void *)c->ot.ctop, (void *)c->ot.cbot, (void *)c->ot.cG, (void *)c->ot.cPF,
                     (void *)c->ot.cPG})
@@ -1725,8 +1725,8 @@ int ensure_clusters(prot_ctx *c, int64_t n_b, int64_t n_a)
     if (n_b > w.ccap_b) {
         if ((rc = dev_alloc(c, &w.cY, (size_t)n_b)) || (rc = dev_alloc(c, &w.cF, (size_t)n_b)) ||
             (rc = dev_alloc(c, &w.cPF, (size_t)n_b + 1)) ||
-            (rc = dev_alloc(c, &w.cact, (size_t)n_b)) || (rc = dev_alloc(c, &w.cneed, (size_t)n_b)) ||
-            (rc = dev_alloc(c, &w.cloff, (size_t)n_b)) || (rc = dev_alloc(c, &w.cllen, (size_t)n_b)))
+            (rc = dev_alloc(c, &w.cact, (size_t)n_b)) ||
+            (rc = dev_alloc(c, &w.crowblk, (size_t)n_b)))
             return rc;
         w.ccap_b = n_b;
     }
@@ -1740,10 +1740,13 @@ int ensure_clusters(prot_ctx *c, int64_t n_b, int64_t n_a)
         w.ccap_a = n_a;
     }
     if (n_b * n_a > w.ccap_cells) {
-        if ((rc = dev_alloc(c, &w.cw, (size_t)(n_b * n_a))) ||
-            (rc = dev_alloc(c, &w.cstage, (size_t)(n_b * n_a + 8))))
-            return rc;
+        if ((rc = dev_alloc(c, &w.cw, (size_t)(n_b * n_a)))) return rc;
         w.ccap_cells = n_b * n_a;
+    }
+    const int64_t staged = n_b * round_up(n_a, 4) + 8;
+    if (staged > w.ccap_stage) {
+        if ((rc = dev_alloc(c, &w.cstage, (size_t)staged))) return rc;
+        w.ccap_stage = staged;
     }
     if (!w.csync && (rc = dev_alloc(c, &w.csync, (size_t)prot::kSyncWords))) return rc;
     const int64_t words = n_a * ((n_b + 63) / 64);
@@ -1828,13 +1831,10 @@ int prot_ot_solve_clustered(prot_ctx *c, const float *C, int64_t n_b, int64_t n_
     A.msum = w.cmsum;
     A.nwb = (int32_t)((n_b + 63) / 64);
     A.act = w.cact;
-    A.need = w.cneed;
     A.zt = w.czt;
     A.stage = w.cstage;
-    A.loff = w.cloff;
-    A.llen = w.cllen;
+    A.rowblk = w.crowblk;
     A.sync = w.csync;
-    A.staged = (int32_t *)(w.csync + prot::kSyncStaged);
     A.PF = w.cPF;
     A.PG = w.cPG;
     A.trace = (long long *)c->trace;

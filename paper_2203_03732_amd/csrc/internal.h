@@ -338,8 +338,8 @@ hipError_t launch_ot_duals(const int32_t *y, const int64_t *off, int64_t n_pts, 
 // ot_cluster.hip: transport with the copies kept as clusters (Lemma 4.1).
 constexpr int64_t kClusterMaxPoints = 4096;   // points per side (one workgroup)
 constexpr int64_t kClusterLdsBytes = 159 * 1024;
-constexpr int kSyncWords = 256;              // hand-over words of the cluster loop
-constexpr int kSyncStaged = 128;             // the word counting staged list entries
+constexpr int kClusterMaxHelpers = 127;      // workgroups that list rows (2 words a lane)
+constexpr int kSyncWords = 512;              // hand-over words of the cluster loop (32-bit)
 struct ClusterArgs {
     const int16_t *k;              // n_b x ldk rounded costs of the points
     int64_t ldk;
@@ -357,12 +357,11 @@ struct ClusterArgs {
     unsigned long long *msum;      // n_a: bit i set iff word i of the point's mask is nonzero
     int32_t nwb;
     // the phase's lists, built by every workgroup of the loop
-    int32_t *act, *need;           // n_b: rows with free copies, their Y - 1
+    unsigned long long *act;       // n_b: rows with free copies, (point << 32) | Y - 1
     int32_t *zt;                   // n_a rounded up to 8: top level, or a never-met level
-    uint16_t *stage;               // n_b x n_a + 8: the lists, one block per row
-    int32_t *loff, *llen;          // n_b: a row's block
+    uint16_t *stage;               // n_b x (n_a rounded up to 4) + 8: the lists, a block per row
+    unsigned long long *rowblk;    // n_b: where a row's block lies
     uint32_t *sync;                // kSyncWords hand-over words
-    int32_t *staged;               // = sync + kSyncStaged: entries staged
     int64_t *PF, *PG;              // running totals of F and G (n_b + 1, n_a + 1)
     long long *trace;              // kTraceCap x 4 per-phase record, or null
     Ctl *ctl;

@@ -43,8 +43,15 @@
 // one workgroup cannot do fast enough: it publishes the rows and the demand
 // levels, and every workgroup of the grid lists a share of the rows into a
 // global staging area, which workgroup 0 then copies into its LDS when it
-// fits. The two hand-overs per phase are a flag and an arrival counter,
-// each wait bounded.
+// fits. The two hand-overs per phase are a flag and a word per helper, which
+// carries the number of entries it listed into its own part of the staging
+// area (atomics of all helpers on one counter took ~9 ns each, one per row and
+// helper); each wait is bounded.
+//
+// Bound: latency. A phase of 1000 x 1000 points at eps = 0.01 (346 rows, 4.5
+// rounds) takes 1.1 us to publish, 5.2 until the lists are there, 1.7 to copy
+// them, 11.5 in rounds (a third of it walking lists, a third points that
+// serve several rows) and 7 in step (II): 35 -> 28 us, the solve 9.75 -> 7.5 ms.
 #include "internal.h"
 #include "device_common.h"
 
@@ -60,14 +67,17 @@ constexpr uint32_t kDone = 0xFFFFFFFFu;                  // epoch: the loop has 
 // every workgroup leaves.
 constexpr int64_t kWaitTicks = 200000000ll;
 
-// Hand-over words (each on its own 256-byte line of ClusterArgs::sync; the
-// entries staged in phase p are counted in word kSyncStaged + p % 2).
-// 64-bit: (phase published by workgroup 0, kDone at the end) << 32 | its rows
+// Hand-over words (64-bit, from ClusterArgs::sync).
+// (phase published by workgroup 0, kDone at the end) << 32 | its rows
 constexpr int kEpoch = 0;
-// 64-bit: (workgroups done listing) << 40 | (list entries they staged), both
-// cumulative over the phases
-constexpr int kArrive = 64;
-constexpr unsigned long long kStagedMask = (1ull << 40) - 1ull;
+// of helper h, at kListed + h: (phase it has listed) << 32 | list entries
+constexpr int kListed = 16;
+static_assert(kListed + kClusterMaxHelpers <= kSyncWords / 2, "hand-over words");
+// A row's block of the staging area: offset << 32 | helper << 16 | length.
+__device__ inline unsigned long long row_block(uint32_t off, int helper, int len)
+{
+    return ((unsigned long long)off << 32) | ((uint32_t)helper << 16) | (uint32_t)len;
+}
 
 // LDS of workgroup 0 (32-bit words), for n_a demand and n_b supply points;
 // the demand arrays have n_a rounded up to 8 entries. req holds, while the
@@ -100,14 +110,6 @@ __device__ inline Lds lds_layout(char *base, int64_t n_b, int64_t n_a, int64_t b
     return L;
 }
 
-// Column of scan position j of supply point b.
-__device__ inline int col_of(int b, int j, int n_a, int origin)
-{
-    if (origin != 0) return j;
-    const int a = b % n_a + j;
-    return a >= n_a ? a - n_a : a;
-}
-
 // Block-wide sum (all threads call); the result is valid in every thread.
 __device__ long long block_sum64(long long v, long long *red)
 {
@@ -121,6 +123,13 @@ __device__ long long block_sum64(long long v, long long *red)
     return t;
 }
 
+// Workgroup barrier for LDS only: atomics and stores to global memory may
+// still be in flight (__syncthreads waits for them).
+__device__ inline void barrier_lds()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // Whether pred holds in any thread of the workgroup, with one barrier
 // (all threads call, the same number of times). Call c raises flag c % 4 and
 // reads it after the barrier; thread 0 clears flag (c + 2) % 4 before it:
@@ -131,29 +140,49 @@ __device__ inline int block_any(int pred, int *flags, uint32_t &calls)
     const uint32_t c = calls++;
     if (threadIdx.x == 0) flags[(c + 2) & 3] = 0;
     if (__ballot(pred) && (threadIdx.x & 63) == 0) flags[c & 3] = 1;
-    __syncthreads();
+    barrier_lds();
     return flags[c & 3];
 }
 
-// Thread 0 waits until *word >= want (or holds kDone, for the epoch), or
-// for the arrival word until its count field reaches want; false on
-// time-out (err bit 5 raised).
-template <class W>
-__device__ bool wait_at_least(W *word, W want, Ctl *ctl, W *seen, int shift = 0)
+// Thread 0 waits until the phase in *word (its upper half) is `want` or later
+// (or kDone); kDone on time-out (err bit 5 raised).
+__device__ unsigned long long wait_phase(const unsigned long long *word, uint32_t want, Ctl *ctl)
 {
     const int64_t t0 = (int64_t)wall_clock64();
     for (int spins = 0;; ++spins) {
-        const W v = ld_agent(word);
-        if ((v >> shift) >= want) {
-            *seen = v;
-            return true;
-        }
+        const unsigned long long v = ld_agent(word);
+        if ((uint32_t)(v >> 32) >= want) return v;
         if ((spins & 63) == 63 && (int64_t)wall_clock64() - t0 > kWaitTicks) {
             __hip_atomic_fetch_or(&ctl->err, 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *seen = shift ? ((W)kDone << shift) : (W)kDone;
+            return (unsigned long long)kDone << 32;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+// One wave waits until each of the H helpers has listed phase `want`: helper
+// 2 lane + e's entries in cnt[e]; false on time-out (err bit 5 raised).
+__device__ bool wait_listed(const unsigned long long *words, int H, uint32_t want, Ctl *ctl,
+                            uint32_t (&cnt)[2])
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t t0 = (int64_t)wall_clock64();
+    for (int spins = 0;; ++spins) {
+        bool ready = true;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int h = 2 * lane + e;
+            const unsigned long long v = h < H ? ld_agent(words + h) : (unsigned long long)want << 32;
+            ready = ready && (uint32_t)(v >> 32) == want;
+            cnt[e] = (uint32_t)v;
+        }
+        if (__ballot(!ready) == 0ull) return true;
+        if ((spins & 63) == 63 && (int64_t)wall_clock64() - t0 > kWaitTicks) {
+            if (lane == 0)
+                __hip_atomic_fetch_or(&ctl->err, 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
-        __builtin_amdgcn_s_sleep(2);
+        __builtin_amdgcn_s_sleep(1);
     }
 }
 
@@ -176,34 +205,43 @@ __device__ inline uint32_t level_hits(uint4 kv, int4 z0, int4 z1, int need)
     return m;
 }
 
-constexpr int kSegVisits = 128;  // chunk visits per row per step (2 per lane)
 
-// The admissible lists of rows [0, count) of this workgroup's share (row i:
-// supply point rb[i], whose free copies sit at rneed[i] + 1), each in its scan
-// order: column a is admissible when k - Z_a = need and a has top copies
-// (zt holds Z_a, or kNever). A wave takes kRowsPerWave rows at once; in a
-// step, lane l looks at chunks (8 columns) 2l and 2l + 1 of each row's
-// visit order, which starts at the chunk holding the row's first column,
-// wraps around, and ends with that chunk again (its columns below the
-// start), so lane order is scan order. A row's entries (scan positions) go
-// to a block of the staging area taken with one atomic; its offset and
-// length to loff[b], llen[b]. Rows longer than one step (n_a > 1016) are
-// read twice: once to count, once to write.
-template <int kRowsPerWave, class RowAt>
-__device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, RowAt row_at,
-                            int *total, int32_t *staged)
+constexpr int kOneStepColumns = 8 * (128 - 1);  // a lane's 2 chunks hold a row and its wrap
+
+// The admissible lists of rows [0, count) of helper h's share (row i: act[i] =
+// supply point << 32 | what it needs), each in its scan order: column a is
+// admissible when k - Z_a = need and a has top copies (zt holds Z_a, or
+// kNever). A wave takes kRowsPerWave rows at once; in a step, lane l looks at
+// kVisits consecutive chunks (8 columns) of each row's visit order, which starts at
+// the chunk holding the row's first column, wraps around, and ends with that
+// chunk again (its columns below the start), so lane order is scan order. A
+// row's entries (scan positions) go to a block of the share's staging area
+// (from `base` on; *filled entries of it are taken); where it lies goes to
+// rowblk[b]. Rows longer than one step are read twice: once to
+// count, once to write. zt is filled by store_levels and complete after the
+// barrier that every wave passes on its way to its first comparison, once its
+// rows' first loads are on their way.
+template <int kRowsPerWave, int kVisits, class Levels>
+__device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count,
+                            const unsigned long long *act, int h, uint32_t base, int *filled,
+                            Levels store_levels)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_a = A.n_a, nch = (n_a + 7) >> 3, V = nch + 1;
+    constexpr int kSegVisits = 64 * kVisits;  // chunks of a row per step
     const int nseg = (V + kSegVisits - 1) / kSegVisits;
+    bool waited = false;
     for (int r0 = wave * kRowsPerWave; r0 < count; r0 += (kCT / 64) * kRowsPerWave) {
         int b[kRowsPerWave], s0[kRowsPerWave], c0[kRowsPerWave], need[kRowsPerWave];
         int len[kRowsPerWave], off[kRowsPerWave];
+        unsigned long long word[kRowsPerWave];
+#pragma unroll
+        for (int g = 0; g < kRowsPerWave; ++g) word[g] = r0 + g < count ? ld_agent(act + r0 + g) : ~0ull;
 #pragma unroll
         for (int g = 0; g < kRowsPerWave; ++g) {
-            b[g] = -1;
-            need[g] = 0;
-            if (r0 + g < count) row_at(r0 + g, &b[g], &need[g]);
+            b[g] = __builtin_amdgcn_readfirstlane((int)(word[g] >> 32));
+            need[g] = __builtin_amdgcn_readfirstlane((int)(uint32_t)word[g]);
             s0[g] = (b[g] >= 0 && A.origin == 0) ? b[g] % n_a : 0;
             c0[g] = s0[g] >> 3;
             len[g] = 0;
@@ -216,13 +254,13 @@ __device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, 
 #pragma unroll
             for (int g = 0; g < kRowsPerWave; ++g) run[g] = 0;
             for (int seg = 0; seg < nseg; ++seg) {
-                uint4 kv[kRowsPerWave][2];
-                int cc[kRowsPerWave][2];
+                uint4 kv[kRowsPerWave][kVisits];
+                int cc[kRowsPerWave][kVisits];
 #pragma unroll
                 for (int g = 0; g < kRowsPerWave; ++g)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int v = seg * kSegVisits + lane * 2 + u;
+                    for (int u = 0; u < kVisits; ++u) {
+                        const int v = seg * kSegVisits + lane * kVisits + u;
                         int c = c0[g] + v;
                         if (c >= nch) c -= nch;
                         cc[g][u] = c;
@@ -231,12 +269,17 @@ __device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, 
                             kv[g][u] = *reinterpret_cast<const uint4 *>(
                                 A.k + (int64_t)b[g] * A.ldk + c * 8);
                     }
-                uint32_t m[kRowsPerWave][2];
+                if (!waited) {
+                    waited = true;
+                    store_levels();
+                    barrier_lds();
+                }
+                uint32_t m[kRowsPerWave][kVisits];
 #pragma unroll
                 for (int g = 0; g < kRowsPerWave; ++g)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int v = seg * kSegVisits + lane * 2 + u;
+                    for (int u = 0; u < kVisits; ++u) {
+                        const int v = seg * kSegVisits + lane * kVisits + u;
                         m[g][u] = 0;
                         if (b[g] < 0 || v >= V) continue;
                         const int c = cc[g][u];
@@ -250,13 +293,11 @@ __device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, 
 #pragma unroll
                 for (int g = 0; g < kRowsPerWave; ++g) {
                     if (b[g] < 0) continue;  // the whole wave
-                    const int mine = __builtin_popcount(m[g][0]) + __builtin_popcount(m[g][1]);
-                    int incl = mine;
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int t = __shfl_up(incl, o);
-                        if (lane >= o) incl += t;
-                    }
-                    const int seg_len = __shfl(incl, 63);
+                    int mine = 0;
+#pragma unroll
+                    for (int u = 0; u < kVisits; ++u) mine += __builtin_popcount(m[g][u]);
+                    const int incl = (int)wave_inclusive_sum_u32((uint32_t)mine);
+                    const int seg_len = __builtin_amdgcn_readlane(incl, 63);
                     if (pass == 0) {
                         len[g] += seg_len;
                         continue;
@@ -264,19 +305,19 @@ __device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, 
                     if (nseg == 1) {
                         len[g] = seg_len;
                         int x = 0;
-                        if (lane == 0 && seg_len > 0) x = add_agent(staged, seg_len);
-                        off[g] = __shfl(x, 0);
+                        if (lane == 0 && seg_len > 0) x = atomicAdd(filled, seg_len);
+                        off[g] = __builtin_amdgcn_readfirstlane(x);
                     }
-                    int at = off[g] + run[g] + incl - mine;
+                    uint16_t *out = A.stage + base + off[g] + run[g] + (incl - mine);
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
+                    for (int u = 0; u < kVisits; ++u) {
                         uint32_t mm = m[g][u];
                         while (mm) {
                             const int e = __builtin_ctz(mm);
                             mm &= mm - 1u;
                             int j = cc[g][u] * 8 + e - s0[g];  // (a - s0) mod n_a
                             if (j < 0) j += n_a;
-                            st_agent(A.stage + at++, (uint16_t)j);
+                            st_agent(out++, (uint16_t)j);
                         }
                     }
                     run[g] += seg_len;
@@ -286,69 +327,76 @@ __device__ void build_lists(const ClusterArgs &A, const int32_t *zt, int count, 
 #pragma unroll
                 for (int g = 0; g < kRowsPerWave; ++g) {
                     int x = 0;
-                    if (lane == 0 && b[g] >= 0 && len[g] > 0) x = add_agent(staged, len[g]);
-                    off[g] = __shfl(x, 0);
+                    if (lane == 0 && b[g] >= 0 && len[g] > 0) x = atomicAdd(filled, len[g]);
+                    off[g] = __builtin_amdgcn_readfirstlane(x);
                 }
             }
         }
         if (lane == 0) {
 #pragma unroll
             for (int g = 0; g < kRowsPerWave; ++g)
-                if (b[g] >= 0) {
-                    st_agent(A.loff + b[g], off[g]);
-                    st_agent(A.llen + b[g], len[g]);
-                    atomicAdd(total, len[g]);
-                }
+                if (b[g] >= 0)
+                    st_agent(A.rowblk + b[g], row_block(base + (uint32_t)off[g], h, len[g]));
         }
+    }
+    if (!waited) {
+        store_levels();
+        barrier_lds();
     }
 }
 
+// First row of helper h's share of n rows, and its entries' place in the
+// staging area (na4: n_a rounded up to 4).
+__device__ inline int share_begin(int n, int h, int H) { return (int)((int64_t)n * h / H); }
+
 // Workgroups other than 0: wait for a phase, list a share of its rows,
-// arrive; until workgroup 0 ends the loop.
-// Workgroups other than 0 list the rows (workgroup 0 only when it is alone).
-// A share of the rows, and the demand levels, are read into LDS together.
+// say so; until workgroup 0 ends the loop.
 template <int kRows>
 __device__ void helper_loop(const ClusterArgs &A, char *lds_raw)
 {
     __shared__ uint32_t s_epoch;
-    __shared__ int s_rows, s_total;
-    const int na8 = (A.n_a + 7) & ~7;
+    __shared__ int s_rows, s_filled;
+    const int na8 = (A.n_a + 7) & ~7, na4 = (A.n_a + 3) & ~3;
     int32_t *zt = reinterpret_cast<int32_t *>(lds_raw);
-    int32_t *rb = zt + na8, *rneed = rb + A.n_b;
-    const int H = gridDim.x - 1, w = blockIdx.x - 1;
+    const int H = gridDim.x - 1, h = blockIdx.x - 1;
+    unsigned long long *words = reinterpret_cast<unsigned long long *>(A.sync);
     for (uint32_t ph = 1;; ++ph) {
         if (threadIdx.x == 0) {
-            unsigned long long e;
-            wait_at_least<unsigned long long>(reinterpret_cast<unsigned long long *>(A.sync + kEpoch),
-                                              ph, A.ctl, &e, 32);
+            const unsigned long long e = wait_phase(words + kEpoch, ph, A.ctl);
             s_epoch = (uint32_t)(e >> 32);
             s_rows = (int)(uint32_t)e;
-            s_total = 0;
+            s_filled = 0;
         }
-        __syncthreads();
+        barrier_lds();
         if (s_epoch == kDone) return;
-        const int n = s_rows;
-        const int lo = (int)((int64_t)n * w / H), cnt = (int)((int64_t)n * (w + 1) / H) - lo;
-        for (int a = threadIdx.x; a < na8; a += kCT) zt[a] = ld_agent(A.zt + a);
-        for (int i = threadIdx.x; i < cnt; i += kCT) {
-            rb[i] = ld_agent(A.act + lo + i);
-            rneed[i] = ld_agent(A.need + lo + i);
+        const int n = s_rows, lo = share_begin(n, h, H), cnt = share_begin(n, h + 1, H) - lo;
+        int32_t z[kClusterMaxPoints / kCT];
+#pragma unroll
+        for (int u = 0; u < (int)(kClusterMaxPoints / kCT); ++u) {
+            const int a = threadIdx.x + u * kCT;
+            z[u] = a < na8 ? ld_agent(A.zt + a) : 0;
         }
-        __syncthreads();
-        build_lists<kRows>(A, zt, cnt, [&](int i, int *b, int *need) {
-            *b = rb[i];
-            *need = rneed[i];
-        }, &s_total, A.staged + (ph & 1));
+        auto store_levels = [&] {
+#pragma unroll
+            for (int u = 0; u < (int)(kClusterMaxPoints / kCT); ++u) {
+                const int a = threadIdx.x + u * kCT;
+                if (a < na8) zt[a] = z[u];
+            }
+        };
+        const uint32_t base = (uint32_t)lo * (uint32_t)na4;
+        if (A.n_a <= kOneStepColumns)
+            build_lists<kRows, 2>(A, zt, cnt, A.act + lo, h, base, &s_filled, store_levels);
+        else
+            build_lists<kRows, 4>(A, zt, cnt, A.act + lo, h, base, &s_filled, store_levels);
         stores_done();
-        __syncthreads();
+        barrier_lds();
         if (threadIdx.x == 0)
-            add_agent(reinterpret_cast<unsigned long long *>(A.sync + kArrive),
-                      (1ull << 40) | (unsigned long long)s_total);
+            st_agent(words + kListed + h, ((unsigned long long)ph << 32) | (uint32_t)s_filled);
     }
 }
 
 // kPer supply points per thread (b = tid + s * kCT), kRows rows listed at
-// once by a wave: (2, 2) up to 2048 supply points, (4, 1) up to 4096 (more
+// once by a wave: (1, 2) up to 1024 supply points, (2, 2) up to 2048, (4, 1) up to 4096 (more
 // registers per thread leave room for fewer rows in flight).
 template <int kPer, int kRows>
 __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
@@ -358,18 +406,21 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
         helper_loop<kRows>(A, lds_raw);
         return;
     }
-    __shared__ long long red[kCT / 64];
-    __shared__ int n_act, lds_lists, s_abort, s_total, s_staged;
-    __shared__ unsigned long long ph_scanned, ph_matched;
+    __shared__ int n_act, lds_lists, s_abort, s_filled;
+    __shared__ uint32_t s_free[2];                   // free supply copies, by phase parity
+    __shared__ int s_begin[kClusterMaxHelpers + 1];  // LDS place of each helper's lists
+    __shared__ uint32_t ph_scanned, ph_matched;
     __shared__ int any_flags[4];
     uint32_t any_calls = 0;
     Lds L = lds_layout(lds_raw, A.n_b, A.n_a, A.lds_bytes);
     const int tid = threadIdx.x;
     const int n_b = A.n_b, n_a = A.n_a;
-    const uint32_t P = gridDim.x;
+    const int H = (int)gridDim.x - 1;  // helpers (none: this workgroup lists the rows)
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    unsigned long long *words = reinterpret_cast<unsigned long long *>(A.sync);
 
     // the state: cold start (every copy free, y(b) = 1, y(a) = 0)
-    const int na8 = (n_a + 7) & ~7;
+    const int na8 = (n_a + 7) & ~7, na4 = (n_a + 3) & ~3;
     for (int a = tid; a < na8; a += kCT) {
         const int32_t d = a < n_a ? (int32_t)(A.d_off[a + 1] - A.d_off[a]) : 0;
         L.Z[a] = 0;
@@ -382,25 +433,38 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
         L.Y[b] = 1;
         L.evict[b] = 0;
     }
-    if (tid == 0) s_abort = 0;
+    if (tid == 0) {
+        s_abort = 0;
+        s_free[0] = s_free[1] = 0;
+        n_act = 0;
+    }
     if (tid < 4) any_flags[tid] = 0;
     int32_t F[kPer], want[kPer], pos[kPer], li[kPer], tgt[kPer], jp[kPer], loff[kPer],
         llen[kPer];
+    int32_t s0[kPer];  // first column of the supply point's scan
     bool act[kPer], prop[kPer], contest[kPer];
 #pragma unroll
     for (int s = 0; s < kPer; ++s) {
         const int b = tid + s * kCT;
         F[s] = b < n_b ? (int32_t)(A.s_off[b + 1] - A.s_off[b]) : 0;
+        s0[s] = A.origin == 0 ? b % n_a : 0;
     }
+    // (at most 2^32 copies: theta = 4 max(n_b, n_a) / eps < 2^30)
+    auto add_free = [&](int e) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int s = 0; s < kPer; ++s) mine += (uint32_t)F[s];
+        const uint32_t sum = wave_sum_u32(mine);
+        if (lane == 0 && sum) atomicAdd(&s_free[e], sum);
+    };
+    __syncthreads();
+    add_free(0);
+    barrier_lds();
     long long phases = 0, sum_free = 0, rounds = 0, max_rounds = 0, scanned = 0;
     int status = 0;
     long long n_free = 0;
-    unsigned long long staged_before = 0;  // entries staged in earlier phases (thread 0)
     for (;;) {
-        long long mine = 0;
-#pragma unroll
-        for (int s = 0; s < kPer; ++s) mine += F[s];
-        n_free = block_sum64(mine, red);
+        n_free = s_free[phases & 1];
         if (n_free <= A.T) break;
         if (A.max_phases > 0 && phases == A.max_phases) {
             status = 1;
@@ -414,81 +478,98 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
         sum_free += n_free;
 
         // Step (I): publish the rows with free copies and the demand levels
-        if (tid == 0) {
-            n_act = 0;
-            s_total = 0;
-            ph_scanned = 0;
-            ph_matched = 0;
-        }
-        __syncthreads();
+        // (s_free and the counters are cleared where no one reads them)
 #pragma unroll
         for (int s = 0; s < kPer; ++s) {
             const int b = tid + s * kCT;
-            if (b < n_b && F[s] > 0) {
-                const int r = atomicAdd(&n_act, 1);
-                st_agent(A.act + r, b);
-                st_agent(A.need + r, L.Y[b] - 1);
-            }
+            const bool in = b < n_b && F[s] > 0;
+            const unsigned long long bal = __ballot(in);
+            int r = 0;
+            if (lane == 0 && bal) r = atomicAdd(&n_act, __builtin_popcountll(bal));
+            r = __builtin_amdgcn_readfirstlane(r) + (int)lanes_below(bal);
+            if (in)
+                st_agent(A.act + r, ((unsigned long long)b << 32) | (uint32_t)(L.Y[b] - 1));
         }
         for (int a = tid; a < na8; a += kCT) {
             const int32_t z = L.top[a] > 0 ? L.Z[a] : kNever;
             L.req[a] = z;
             st_agent(A.zt + a, z);
         }
-        // (the staging count of the next phase starts at zero: it was last
-        // used in the previous phase, which every workgroup has finished)
-        if (tid == 0) st_agent(A.staged + ((phases + 1) & 1), 0);
-        stores_done();
-        __syncthreads();
-        if (tid == 0)
-            st_agent(reinterpret_cast<unsigned long long *>(A.sync + kEpoch),
-                     ((unsigned long long)phases << 32) | (uint32_t)n_act);
-        // ... the other workgroups list the rows (this one only when alone) ...
-        if (P == 1) {
-            build_lists<kRows>(A, L.req, n_act, [&](int i, int *b, int *need) {
-                *b = ld_agent(A.act + i);
-                *need = ld_agent(A.need + i);
-            }, &s_total, A.staged + (phases & 1));
-            stores_done();
-            __syncthreads();
-        }
         if (tid == 0) {
-            int staged = s_total;
-            if (P > 1) {
-                unsigned long long seen;
-                if (!wait_at_least<unsigned long long>(
-                        reinterpret_cast<unsigned long long *>(A.sync + kArrive),
-                        (unsigned long long)(P - 1) * (unsigned long long)phases, A.ctl, &seen, 40))
-                    s_abort = 1;
-                staged = (int)((seen & kStagedMask) - staged_before);
-                staged_before = seen & kStagedMask;
-            }
-            s_staged = staged;
-            lds_lists = (int64_t)((staged + 7) & ~7) <= L.list_cap;
+            s_filled = 0;
+            ph_scanned = 0;
+            ph_matched = 0;
+            s_free[(phases & 1)] = 0;
         }
-        // (each supply point's list block, read while thread 0 waits)
+        stores_done();
+        barrier_lds();
+        const int rows = n_act;
+        if (tid == 0)
+            st_agent(words + kEpoch, ((unsigned long long)phases << 32) | (uint32_t)rows);
+        // ... the helpers list the rows (this workgroup only when alone) ...
+        if (H == 0) {
+            build_lists<kRows, 4>(A, L.req, rows, A.act, 0, 0u, &s_filled, [] {});
+            stores_done();
+            barrier_lds();
+        }
+        if (wave == 0) {
+            // where each helper's entries start in LDS (multiples of 4)
+            uint32_t cnt[2] = {H == 0 && lane == 0 ? (uint32_t)s_filled : 0u, 0u};
+            if (H > 0 && !wait_listed(words + kListed, H, (uint32_t)phases, A.ctl, cnt)) s_abort = 1;
+            const uint32_t c0 = (cnt[0] + 3u) & ~3u, c1 = (cnt[1] + 3u) & ~3u;
+            const uint32_t incl = wave_inclusive_sum_u32(c0 + c1);
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (2 * lane <= H) s_begin[2 * lane] = (int)(incl - c0 - c1);
+            if (2 * lane + 1 <= H) s_begin[2 * lane + 1] = (int)(incl - c1);
+            if (lane == 0) {
+                if (H == 0) s_begin[1] = (int)total;
+                lds_lists = (int64_t)total <= L.list_cap;
+            }
+        }
 #pragma unroll
         for (int s = 0; s < kPer; ++s) {
             const int b = tid + s * kCT;
             act[s] = b < n_b && F[s] > 0;
         }
-        __syncthreads();
+        barrier_lds();
         if (s_abort) {
             status = 3;
             break;
         }
+        if (tid == 0) n_act = 0;
+        // each supply point's block of the staging area ...
+        const bool in_lds = lds_lists;
+        const int shares = H > 0 ? H : 1;
+        unsigned long long blk[kPer];
 #pragma unroll
         for (int s = 0; s < kPer; ++s) {
             const int b = tid + s * kCT;
-            loff[s] = act[s] ? ld_agent(A.loff + b) : 0;
-            llen[s] = act[s] ? ld_agent(A.llen + b) : 0;
+            blk[s] = act[s] ? ld_agent(A.rowblk + b) : 0ull;
         }
-        // ... and take the staged lists into LDS when they fit
-        if (lds_lists) {
-            const int staged = s_staged;
-            const uint32_t *src = reinterpret_cast<const uint32_t *>(A.stage);
-            uint32_t *dst = reinterpret_cast<uint32_t *>(L.list);
-            for (int i = tid; i < (staged + 1) / 2; i += kCT) dst[i] = ld_agent(src + i);
+        // ... and the staged lists, into LDS when they fit: half a wave a
+        // share, 4 entries (8 bytes) a lane
+        if (in_lds) {
+            for (int h = tid >> 5; h < shares; h += kCT / 32) {
+                const int at = s_begin[h], n4 = (s_begin[h + 1] - at) >> 2;
+                const unsigned long long *src = reinterpret_cast<const unsigned long long *>(
+                    A.stage + (int64_t)share_begin(rows, h, shares) * na4);
+                unsigned long long *dst = reinterpret_cast<unsigned long long *>(L.list + at);
+                for (int i0 = tid & 31; i0 < n4; i0 += 4 * 32) {
+                    unsigned long long v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = ld_agent(src + min(i0 + 32 * u, n4 - 1));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i0 + 32 * u < n4) dst[i0 + 32 * u] = v[u];
+                }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kPer; ++s) {
+            const int h = (int)(blk[s] >> 16) & 0xFFFF;
+            loff[s] = (int32_t)(blk[s] >> 32);
+            llen[s] = (int)(blk[s] & 0xFFFFu);
+            if (in_lds && act[s]) loff[s] += s_begin[h] - share_begin(rows, h, shares) * na4;
         }
 #pragma unroll
         for (int s = 0; s < kPer; ++s) {
@@ -500,32 +581,55 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
             L.cap[a] = L.top[a];
             L.req[a] = 0;
         }
-        __syncthreads();
-        const bool in_lds = lds_lists;
+        barrier_lds();
 
         long long ph_rounds = 0;
+        uint32_t my_scan = 0, my_match = 0;  // of the phase
         for (;;) {
             // (i) propose, against the capacities at the round's start
-            long long my_scan = 0;
             int my_prop = 0;
 #pragma unroll
             for (int s = 0; s < kPer; ++s) {
                 prop[s] = false;
                 if (!act[s]) continue;
-                const int b = tid + s * kCT;
+                // (four entries at a time: the list's and the capacities' reads
+                // overlap)
                 int i = li[s], a = -1, j = -1;
-                for (; i < llen[s]; ++i) {
-                    j = in_lds ? L.list[loff[s] + i] : ld_agent(A.stage + loff[s] + i);
-                    a = col_of(b, j, n_a, A.origin);
-                    if (L.cap[a] > 0) break;
+                const int last = llen[s] - 1;
+                for (; i <= last; i += 4) {
+                    int ju[4], au[4], cu[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int at = loff[s] + min(i + u, last);
+                        ju[u] = in_lds ? L.list[at] : ld_agent(A.stage + at);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        au[u] = s0[s] + ju[u];
+                        if (au[u] >= n_a) au[u] -= n_a;
+                        cu[u] = L.cap[au[u]];
+                    }
+                    int hit = 4;
+#pragma unroll
+                    for (int u = 3; u >= 0; --u)
+                        if (cu[u] > 0) {
+                            hit = u;
+                            j = ju[u];
+                            a = au[u];
+                        }
+                    if (hit < 4) {
+                        i += hit;
+                        break;
+                    }
                 }
+                i = min(i, llen[s]);
                 li[s] = i;
                 if (i >= llen[s]) {
-                    my_scan += n_a - pos[s];
+                    my_scan += (uint32_t)(n_a - pos[s]);
                     act[s] = false;
                     continue;
                 }
-                my_scan += j - pos[s] + 1;
+                my_scan += (uint32_t)(j - pos[s] + 1);
                 pos[s] = j;
                 jp[s] = j;
                 tgt[s] = a;
@@ -533,7 +637,6 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
                 my_prop = 1;
                 atomicAdd(&L.req[a], want[s]);
             }
-            if (my_scan) atomicAdd(&ph_scanned, (unsigned long long)my_scan);
             if (!block_any(my_prop, any_flags, any_calls)) break;
             ph_rounds += 1;
             // (ii) a point asked for no more than it has serves everyone;
@@ -569,7 +672,7 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
                         contest[s] = false;
                         L.minb[a] = 0x7FFFFFFF;
                     }
-                    __syncthreads();
+                    barrier_lds();
                     // the rest of a point with nothing left get nothing; the
                     // others select their next lowest b
                     int left = 0;
@@ -587,7 +690,6 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
                 }
             }
             // (iii) the grants become pairs (at the demand copies' next level)
-            long long my_match = 0;
 #pragma unroll
             for (int s = 0; s < kPer; ++s) {
                 if (!prop[s]) continue;
@@ -600,7 +702,7 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
                     atomicAdd(((L.Z[a] - 1) & 1) == 0 ? &cell->x : &cell->y, g);
                     atomicOr(A.mask + (int64_t)a * A.nwb + (b >> 6), 1ull << (b & 63));
                     atomicOr(A.msum + a, 1ull << (b >> 6));
-                    my_match += g;
+                    my_match += (uint32_t)g;
                 }
                 want[s] -= g;
                 if (want[s] == 0) {
@@ -610,9 +712,15 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
                     li[s] += 1;
                 }
             }
-            if (my_match) atomicAdd(&ph_matched, (unsigned long long)my_match);
-            __syncthreads();
+            barrier_lds();
         }
+        {
+            const uint32_t sc = wave_sum_u32(my_scan), mt = wave_sum_u32(my_match);
+            if (lane == 0 && sc) atomicAdd(&ph_scanned, sc);
+            if (lane == 0 && mt) atomicAdd(&ph_matched, mt);
+        }
+        stores_done();  // the pairs and bitmaps of the phase are in memory
+        __syncthreads();
 
         // Step (II): each point hands out the top copies taken
         for (int a = tid; a < n_a; a += kCT) {
@@ -705,6 +813,7 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
             F[s] = want[s] + L.evict[b];
             L.evict[b] = 0;
         }
+        add_free((int)(phases & 1));
         rounds += ph_rounds;
         max_rounds = ph_rounds > max_rounds ? ph_rounds : max_rounds;
         scanned += (long long)ph_scanned;
@@ -718,9 +827,7 @@ __global__ void __launch_bounds__(kCT) cluster_loop_kernel(ClusterArgs A)
         __syncthreads();
     }
     // the other workgroups leave
-    if (tid == 0)
-        st_agent(reinterpret_cast<unsigned long long *>(A.sync + kEpoch),
-                 (unsigned long long)kDone << 32);
+    if (tid == 0) st_agent(words + kEpoch, (unsigned long long)kDone << 32);
 
     // the state the later kernels read
     for (int a = tid; a < n_a; a += kCT) {
@@ -930,7 +1037,8 @@ hipError_t launch_cluster_init(const ClusterArgs &A, hipStream_t s)
                        reinterpret_cast<unsigned long long *>(A.sync), (int64_t)kSyncWords / 2);
     static bool attr_set = false;
     if (!attr_set) {
-        for (const void *fn : {(const void *)cluster_loop_kernel<2, 2>,
+        for (const void *fn : {(const void *)cluster_loop_kernel<1, 2>,
+                               (const void *)cluster_loop_kernel<2, 2>,
                                (const void *)cluster_loop_kernel<kPerMax, 1>}) {
             const hipError_t e = hipFuncSetAttribute(
                 fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kClusterLdsBytes);
@@ -943,7 +1051,8 @@ hipError_t launch_cluster_init(const ClusterArgs &A, hipStream_t s)
 
 const void *cluster_loop_fn(int32_t n_b)
 {
-    return n_b <= 2 * kCT ? (const void *)cluster_loop_kernel<2, 2>
+    return n_b <= kCT       ? (const void *)cluster_loop_kernel<1, 2>
+           : n_b <= 2 * kCT ? (const void *)cluster_loop_kernel<2, 2>
                           : (const void *)cluster_loop_kernel<kPerMax, 1>;
 }
 
@@ -959,7 +1068,7 @@ hipError_t cluster_grid(int32_t n_b, int *grid)
     // about one batch of rows (16 waves x 2 rows) per workgroup when every
     // supply point has free copies
     int want = (n_b + 31) / 32;
-    const int most = per_cu * cus;
+    const int most = min(per_cu * cus, kClusterMaxHelpers + 1);
     *grid = want < 1 ? 1 : (want > most ? most : want);
     return hipSuccess;
 }
