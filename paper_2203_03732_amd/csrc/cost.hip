@@ -704,7 +704,192 @@ __device__ __forceinline__ void points_tile(const PointsJob &j, int64_t b0, int6
 template <int PASS, bool L1 = false>
 __global__ void __launch_bounds__(256) points_tile_kernel(PointsJob j)
 {
-    points_tile<PASS, L1>(j, (int64_t)blockIdx.y * kTile, (int64_t)blockIdx.x * kTile);
+    // (column tiles shifted as in points_wide_kernel)
+    const unsigned col_tile = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+    points_tile<PASS, L1>(j, (int64_t)blockIdx.y * kTile, (int64_t)col_tile * kTile);
+}
+
+// The same for many pairs: a block takes 128 x 128 pairs, each wave a 64 x 64
+// quadrant (skipped if it holds no pair), each thread 8 x 8 pairs. The
+// arithmetic of a pair is that of points_tile.
+// Bound: instruction issue, 2 d a pair for the sum; a thread of 4 x 4 pairs
+// needs ~20 more a pair at d = 16 for staging, addresses, the maximum or the
+// rounding and the constants of both, one of 8 x 8 a third of that. 512
+// instances of n in [64, 1024], d = 16: maximum 324 -> 213 us, rounding 344 -> 252
+// (of it a third from the shift of the column tiles below); 16,384 x 16,384: 230 and 250.
+constexpr int kWide = 128;
+constexpr int64_t kWideMinN = 257, kWideMinTiles = 1536;
+
+template <int PASS, bool kVec>
+__global__ void __launch_bounds__(256) points_wide_kernel(PointsJob j)
+{
+    __shared__ __align__(16) float xs[kTj][kWide + 4];
+    __shared__ __align__(16) float ys[kTj][kWide + 4];
+    __shared__ float red[4];
+    const Instance in = j.instance(blockIdx.z);
+    const int64_t n = in.n, na = in.na;  // rows, columns
+    // Consecutive blocks run on consecutive XCDs: without the shift the column
+    // tiles that only large instances have would all be one XCD's.
+    const unsigned col_tile = (blockIdx.x + blockIdx.y + blockIdx.z) % gridDim.x;
+    const int64_t b0 = (int64_t)blockIdx.y * kWide, a0 = (int64_t)col_tile * kWide;
+    if (b0 >= n || a0 >= (PASS ? in.ldk : na)) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int d = j.d;
+    // the wave's quadrant: waves of one number share a SIMD, and the quadrants
+    // past an instance's edge are always the last, so the numbers are dealt round
+    const int quadrant = (wave + (int)(blockIdx.x + 2 * blockIdx.y + blockIdx.z)) & 3;
+    const int qr = (quadrant >> 1) * 64, qc = (quadrant & 1) * 64;
+    const int r8 = qr + (lane >> 3) * 8, c8 = qc + (lane & 7) * 8;
+    const bool live = b0 + qr < n && a0 + qc < na;
+    float acc[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[i][c] = 0.0f;
+    // staging: half a row's 16 coordinates per thread
+    const int sr = tid >> 1, sj = (tid & 1) * 8;
+    const float *xrow = in.X + (b0 + sr < n ? b0 + sr : 0) * d;
+    const float *yrow = in.Y + (a0 + sr < na ? a0 + sr : 0) * d;
+    const bool xin = b0 + sr < n, yin = a0 + sr < na;
+    for (int j0 = 0; j0 < d; j0 += kTj) {
+        float xv[8], yv[8];
+        if constexpr (kVec) {
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                const int jj = j0 + sj + h;
+                const bool cj = jj < d;  // (d is a multiple of 4)
+                const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                const float4 x = cj && xin ? *reinterpret_cast<const float4 *>(xrow + jj) : z;
+                const float4 y = cj && yin ? *reinterpret_cast<const float4 *>(yrow + jj) : z;
+                xv[h] = x.x, xv[h + 1] = x.y, xv[h + 2] = x.z, xv[h + 3] = x.w;
+                yv[h] = y.x, yv[h + 1] = y.y, yv[h + 2] = y.z, yv[h + 3] = y.w;
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                const int jj = j0 + sj + h;
+                xv[h] = jj < d && xin ? xrow[jj] : 0.0f;
+                yv[h] = jj < d && yin ? yrow[jj] : 0.0f;
+            }
+        }
+        if (j0) __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+            xs[sj + h][sr] = xv[h];
+            ys[sj + h][sr] = yv[h];
+        }
+        __syncthreads();
+        if (live) {
+            const int top = min(kTj, d - j0);
+#pragma unroll 4
+            for (int jj = 0; jj < top; ++jj) {
+                const float4 x0 = *reinterpret_cast<const float4 *>(&xs[jj][r8]);
+                const float4 x1 = *reinterpret_cast<const float4 *>(&xs[jj][r8 + 4]);
+                const float4 y0 = *reinterpret_cast<const float4 *>(&ys[jj][c8]);
+                const float4 y1 = *reinterpret_cast<const float4 *>(&ys[jj][c8 + 4]);
+                const float xr[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                const float yc[8] = {y0.x, y0.y, y0.z, y0.w, y1.x, y1.y, y1.z, y1.w};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        const float t = __fsub_rn(xr[i], yc[c]);
+                        acc[i][c] = __fmaf_rn(t, t, acc[i][c]);
+                    }
+            }
+        }
+    }
+    if constexpr (PASS == 0) {
+        float mx = 0.0f;
+        bool bad = false;
+        if (live) {
+            // as unsigned bits sums (>= 0) keep their order, and an infinity or
+            // a NaN of either sign exceeds every finite one
+            uint32_t top = 0u;
+            if (b0 + qr + 64 <= n && a0 + qc + 64 <= na) {  // the whole quadrant
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) top = max(top, __float_as_uint(acc[i][c]));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (b0 + r8 + i >= n) continue;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c)
+                        if (a0 + c8 + c < na) top = max(top, __float_as_uint(acc[i][c]));
+                }
+            }
+            mx = fmaxf(0.0f, __uint_as_float(top));  // (0 for a NaN)
+            bad = top > __float_as_uint(FLT_MAX);
+        }
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        if (lane == 0) red[wave] = mx;
+        __syncthreads();
+        if (tid == 0) {
+            const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+            __hip_atomic_fetch_max(reinterpret_cast<unsigned *>(&j.m[blockIdx.z]),
+                                   __float_as_uint(m), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (bad) __hip_atomic_fetch_or(j.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        if (b0 + qr >= n || a0 + c8 >= in.ldk) return;  // (no barrier follows)
+        const float mf = j.m[blockIdx.z];
+        const int32_t K = (mf > 0.0f) ? (int32_t)floor(1.0 / j.eps) : 0;
+        const bool euclid = j.metric == 1;
+        const float inv = (mf > 0.0f) ? (float)(1.0 / ((euclid ? sqrt((double)mf) : (double)mf) *
+                                                         j.eps))
+                                      : 0.0f;
+        const float delta = classify_margin(K);
+        const float *th = j.th + (int64_t)blockIdx.z * j.kcap;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t row = b0 + r8 + i;
+            if (row >= n) continue;
+            int g[8];
+            if (euclid) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    g[c] = refine_k(acc[i][c], (int)__fmul_rn(__fsqrt_rn(acc[i][c]), inv), K, th);
+            } else {
+                // fast_k of eight: how far the products' fractions get from 1/2
+                float off = 0.0f;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const float v = __fmul_rn(acc[i][c], inv);
+                    off = fmaxf(off, fabsf(__builtin_amdgcn_fractf(v) - 0.5f));
+                    g[c] = (int)v;
+                }
+                // (a guess that is far enough from every integer stays what it
+                // is; a NaN's fraction would not show in the maximum, but then
+                // the build is in error)
+                if (!(off <= 0.5f - delta - 1.2e-7f))
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) g[c] = refine_k(acc[i][c], g[c], K, th);
+            }
+            if (a0 + c8 + 8 > na)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    if (a0 + c8 + c >= na) g[c] = 0x7FFF;
+            if (j.k8) {
+                uint32_t q[8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) q[c] = (uint32_t)g[c] > 255u ? 255u : (uint32_t)g[c];
+                *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(in.k) + row * in.ldk + a0 + c8) =
+                    make_uint2(q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24),
+                               q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24));
+            } else {
+                uint32_t q[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    q[c] = (uint32_t)(uint16_t)g[2 * c] | ((uint32_t)(uint16_t)g[2 * c + 1] << 16);
+                *reinterpret_cast<uint4 *>(in.k + row * in.ldk + a0 + c8) =
+                    make_uint4(q[0], q[1], q[2], q[3]);
+            }
+        }
+    }
 }
 
 // The settling tiles of the screened L1 build whose lists overflowed, every
@@ -724,6 +909,25 @@ __global__ void __launch_bounds__(256) points_tile_overflow_kernel(PointsJob j)
 void launch_points_tiled(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
 {
     const unsigned rows = (unsigned)((n_max + kTile - 1) / kTile);
+    // Wide tiles where there is work for them on every compute unit (one takes
+    // as long as four small ones in turn) and little of it lies past the edge.
+    // Whole calls, small / wide tiles: n = 2,500, d = 8 (1,600 small tiles) 111 /
+    // 98 us, 64 x 300, d = 8 (1,600) 106 / 101, 64 x 2,000 1,102 / 722; but
+    // 32 x 300 (800) 103 / 111, n = 1,100 (324) 93 / 98, 512 x 129 (4,608, half
+    // of a wide tile empty) 159 / 182.
+    if (n_max >= kWideMinN && (int64_t)rows * rows * j.batch >= kWideMinTiles) {
+        const unsigned wide_rows = (unsigned)((n_max + kWide - 1) / kWide);
+        const bool vec = j.d % 4 == 0 && (((uintptr_t)j.X | (uintptr_t)j.Y) & 15) == 0;
+        const dim3 gm(wide_rows, wide_rows, j.batch);
+        const dim3 gk((unsigned)((ldk_max + kWide - 1) / kWide), wide_rows, j.batch);
+        hipLaunchKernelGGL(vec ? (points_wide_kernel<0, true>) : (points_wide_kernel<0, false>),
+                           gm, dim3(256), 0, s, j);
+        hipLaunchKernelGGL(thresholds_kernel, dim3(threshold_blocks(j.kcap), 1, j.batch),
+                           dim3(256), 0, s, j);
+        hipLaunchKernelGGL(vec ? (points_wide_kernel<1, true>) : (points_wide_kernel<1, false>),
+                           gk, dim3(256), 0, s, j);
+        return;
+    }
     hipLaunchKernelGGL(points_tile_kernel<0>, dim3(rows, rows, j.batch), dim3(256), 0, s, j);
     hipLaunchKernelGGL(thresholds_kernel, dim3(threshold_blocks(j.kcap), 1, j.batch), dim3(256),
                        0, s, j);
