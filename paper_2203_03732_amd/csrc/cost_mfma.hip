@@ -7,8 +7,8 @@
 // of pairs per workgroup: four waves, each a 64 x 64 quarter made of 2 x 2
 // blocks of v_mfma_f32_32x32x2_f32, so that every operand read from LDS
 // feeds two matrix instructions. The tile's coordinates are staged through
-// LDS 64 at a time, transposed (coordinate-major), so that the 32 lanes
-// reading one operand column touch 32 consecutive words; for d <= 64 the
+// LDS 32 at a time, transposed (coordinate-major), so that the 32 lanes
+// reading one operand column touch 32 consecutive words; for d <= 32 the
 // whole tile stays in LDS, where the exact recomputations read it. The squared norms
 // of the tile's rows and columns are summed from the same staged values.
 // Standard floating-point error bounds give |a - s| <= (2d + 6) u (|x| +
@@ -35,8 +35,14 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kT = (int)kMfmaTile;  // tile rows and columns (128)
-constexpr int kKC = 64;              // coordinates staged per step (d <= 64: all of them)
-constexpr int kList = 2048;          // uncertain entries of a tile settled together
+// coordinates staged per step (d <= kKC: all of them). 32, not 64: half the LDS
+// and three or four workgroups a compute unit instead of two, so that one's
+// matrix instructions run while another stages or classifies (64 x 2,048, d = 64,
+// eps = 0.05: maximum 633 -> 509 us, 16 566; rounding, with registers for four, 868 -> 606).
+constexpr int kKC = 32;
+// uncertain entries of a tile settled together (as many as leave the rounding
+// pass's LDS at a quarter of a compute unit's)
+constexpr int kList = 7 * 256;
 constexpr int kLd = kT + 4;          // floats per staged coordinate (row of the transposed stage)
 constexpr int kKs = kT + 8;          // int16 per row of the output tile
 
@@ -269,7 +275,7 @@ __global__ void __launch_bounds__(256) mfma_exact_max_kernel(PointsJob j, MfmaAu
 }
 
 // Pass C: rounded costs; uncertain pairs are recomputed with the definition.
-__global__ void __launch_bounds__(256) mfma_k_kernel(PointsJob j, MfmaAux x)
+__global__ void __launch_bounds__(256, 4) mfma_k_kernel(PointsJob j, MfmaAux x)
 {
     __shared__ __align__(16) char lds[kTileLds];
     __shared__ float nx[kT], ny[kT], sx[kT], sy[kT];
@@ -280,7 +286,6 @@ __global__ void __launch_bounds__(256) mfma_k_kernel(PointsJob j, MfmaAux x)
     tile_dots(in, j.d, b0, a0, *reinterpret_cast<StageLds *>(lds), nx, ny, sx, sy, acc);
     StageLds &st = *reinterpret_cast<StageLds *>(lds);
     __shared__ uint16_t list[kList];     // tile positions r * kT + c to settle
-    __shared__ int16_t settled[kList];   // their rounded costs
     __shared__ uint32_t s_cnt;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const float mf = j.m[blockIdx.z];
@@ -295,7 +300,16 @@ __global__ void __launch_bounds__(256) mfma_k_kernel(PointsJob j, MfmaAux x)
     auto settle = [&](int r, int c, bool lds_ok) -> int {
         float s = 0.0f;
         if (lds_ok) {
-            for (int k = 0; k < j.d; ++k) {
+            // (a sequential chain; eight coordinates' reads go out ahead of it)
+            int k = 0;
+            for (; k + 8 <= j.d; k += 8) {
+                float t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t[u] = __fsub_rn(st.xs[k + u][r], st.ys[k + u][c]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s = __fmaf_rn(t[u], t[u], s);
+            }
+            for (; k < j.d; ++k) {
                 const float t = __fsub_rn(st.xs[k][r], st.ys[k][c]);
                 s = __fmaf_rn(t, t, s);
             }
@@ -337,9 +351,12 @@ __global__ void __launch_bounds__(256) mfma_k_kernel(PointsJob j, MfmaAux x)
     __syncthreads();
     // the listed entries with the definition, spread over the workgroup
     const uint32_t cnt = min(s_cnt, (uint32_t)kList);
-    for (uint32_t i = threadIdx.x; i < cnt; i += 256) {
-        const int pos = list[i];
-        settled[i] = (int16_t)settle(pos / kT, pos % kT, resident);
+    int settled[kList / 256];
+#pragma unroll
+    for (int u = 0; u < kList / 256; ++u) {
+        const uint32_t i = threadIdx.x + 256u * u;
+        settled[u] = 0;
+        if (i < cnt) settled[u] = settle(list[i] / kT, list[i] % kT, resident);
     }
     // every read of the staged coordinates is done: the rounded tile takes
     // their place
@@ -354,9 +371,10 @@ __global__ void __launch_bounds__(256) mfma_k_kernel(PointsJob j, MfmaAux x)
             const int g = __float_as_int(acc[q][v]);
             if (g != -1) ks[r][c] = (int16_t)g;
         }
-    for (uint32_t i = threadIdx.x; i < cnt; i += 256) {
-        const int pos = list[i];
-        ks[pos / kT][pos % kT] = settled[i];
+#pragma unroll
+    for (int u = 0; u < kList / 256; ++u) {
+        const uint32_t i = threadIdx.x + 256u * u;
+        if (i < cnt) ks[list[i] / kT][list[i] % kT] = (int16_t)settled[u];
     }
     __syncthreads();
     if (s_cnt > (uint32_t)kList) {
