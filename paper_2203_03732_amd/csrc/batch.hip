@@ -39,12 +39,15 @@
 #include "device_common.h"
 #include "internal.h"
 
+#include <type_traits>
+
 namespace prot {
 namespace {
 
 constexpr uint32_t kListFill = 0x7FFF0000u;  // column 0 with a k that never matches
 constexpr uint16_t kNone16 = 0xFFFF;
 constexpr int32_t kBatchWideMax = 256;
+constexpr int32_t kBatchNarrowMaxN = 256, kBatchNarrowMin = 1024;
 // A column's key: the round above the proposing row in reverse order, so that
 // the larger key wins and within a round the smaller row. A key of an earlier
 // round never wins, so keys are not cleared between rounds; before the round
@@ -905,13 +908,23 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
 
 __global__ void batch_reset_kernel(unsigned int *queue) { *queue = 0u; }
 
-// The variant for a batch: n_max picks the LDS layout.
+// The variant for a batch: n_max picks the LDS layout and the registers a row
+// takes, the batch the waves an instance gets: 16 while every instance has a
+// compute unit to itself, 8 beyond, 4 for many small ones. Whole calls in us
+// with layouts of 1,024 -> 512 columns: 10 x 500 407 -> 374, 8 x 256 235 -> 218
+// (16 waves); 512 x [300, 500] 554 -> 508 (8 waves; 16: 593, 4: 608);
+// 2,000 x [100, 256], 8 -> 4 waves 649 -> 585, but 306 x [39, 247] 174 -> 215.
 template <class F>
 auto with_batch_kernel(int32_t n_max, int32_t batch, F f)
 {
     if (n_max > 1024) return f(batch_solve_kernel<2048, 1024>, 1024);
-    return batch > kBatchWideMax ? f(batch_solve_kernel<1024, 512>, 512)
-                                 : f(batch_solve_kernel<1024, 1024>, 1024);
+    if (n_max > 512)
+        return batch > kBatchWideMax ? f(batch_solve_kernel<1024, 512>, 512)
+                                     : f(batch_solve_kernel<1024, 1024>, 1024);
+    if (batch <= kBatchWideMax) return f(batch_solve_kernel<512, 1024>, 1024);
+    return n_max <= kBatchNarrowMaxN && batch >= kBatchNarrowMin
+               ? f(batch_solve_kernel<512, 256>, 256)
+               : f(batch_solve_kernel<512, 512>, 512);
 }
 
 }  // namespace
@@ -922,11 +935,13 @@ hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hi
 {
     SoloArgs copy = a;
     void *args[] = {&copy};
-    const void *fn =
-        a.n_a > 1024 ? (a.k8 ? (const void *)solo_kernel<2048, 1024, kSoloListCap, true>
-                             : (const void *)solo_kernel<2048, 1024, kSoloListCap, false>)
-                     : (a.k8 ? (const void *)solo_kernel<1024, 1024, kSoloListCap, true>
-                             : (const void *)solo_kernel<1024, 1024, kSoloListCap, false>);
+    auto pick = [&](auto bytes) -> const void * {
+        constexpr bool kBytes = decltype(bytes)::value;
+        return a.n_a > 1024  ? (const void *)solo_kernel<2048, 1024, kSoloListCap, kBytes>
+               : a.n_a > 512 ? (const void *)solo_kernel<1024, 1024, kSoloListCap, kBytes>
+                             : (const void *)solo_kernel<512, 1024, kSoloListCap, kBytes>;
+    };
+    const void *fn = a.k8 ? pick(std::true_type{}) : pick(std::false_type{});
     return hipExtLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s, ev_start, ev_stop, 0);
 }
 
