@@ -227,7 +227,7 @@ int ensure_loop(prot_ctx *c, int64_t n)
     if ((rc = dev_alloc(c, &c->lists, (size_t)cap * 2))) return rc;
     if ((rc = dev_alloc(c, &c->tlists, (size_t)cap * 4 * prot::kMaxGroups))) return rc;
     if (!c->solo_lists &&
-        (rc = dev_alloc(c, &c->solo_lists, (size_t)prot::kSoloMaxN * prot::kSoloListCap)))
+        (rc = dev_alloc(c, &c->solo_lists, (size_t)prot::kSoloMaxN * (prot::kSoloListCap + 1))))
         return rc;
     // list entries carry tags; fresh memory must not hold one by chance
     HIP_TRY(c, prot::launch_fill_u64(c->tlists, cap * 4 * prot::kMaxGroups, 0ull, c->stream));
@@ -521,12 +521,14 @@ int next_loop_events(prot_ctx *c, hipEvent_t **out)
 // The phase loop on n rows (B) and n_a >= n columns (A), with its init and
 // finish kernels. K: the largest rounded cost (for the watchdog and the
 // warm-start check). cooperative: launch the loop cooperatively (the retry after the gate
-// admitted too few workgroups).
+// admitted too few workgroups). first_lists: rows are expected to have few
+// columns at their smallest costs (the one-workgroup solver's lists are made
+// beforehand).
 int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk, int64_t T,
              const prot_opts *o, int32_t warm, int32_t *mate_a, int32_t *mate_b, int32_t *y_a,
              int32_t *y_b, int64_t K, bool cooperative = false,
              const OnTheFly &otf = OnTheFly(), const Copies &cp = Copies(), int k8 = 0,
-             int64_t trace_off = 0)
+             int64_t trace_off = 0, bool first_lists = false)
 {
     int rc = ensure_loop(c, n_a);
     if (rc) return rc;
@@ -633,6 +635,9 @@ int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk,
         so.max_phases = a.max_phases;
         so.phase_bound = a.phase_bound;
         so.lists = c->solo_lists;
+        so.first = first_lists && n_a <= 2 * n
+                       ? c->solo_lists + prot::kSoloMaxN * prot::kSoloListCap
+                       : nullptr;
         so.ctl = c->ctl;
         so.trace = a.trace;
         so.mate_a = mate_a;
@@ -777,7 +782,8 @@ struct prot_batch {
     int32_t kcap = 0;
     int32_t *err = nullptr;
     unsigned int *queue = nullptr;
-    uint32_t *lists = nullptr;       // candidate lists of the LDS engine
+    uint32_t *lists = nullptr;       // candidate lists of the LDS engine, then the first ones' bounds
+    int64_t list_rows = 0;
     int64_t phase_bound = 0;         // its watchdog (BatchArgs)
     prot_instance_stats *stats_tmp = nullptr;
     float *mfma_buf = nullptr;
@@ -990,6 +996,9 @@ int batch_enqueue(prot_batch *bp, hipStream_t s, const float *X, const float *Y,
     a.stats = reinterpret_cast<prot::InstanceStats *>(stats ? stats : bp->stats_tmp);
     a.queue = bp->queue;
     a.lists = bp->lists;
+    a.first = prot::batch_first_lists(bp->batch, bp->d)
+                  ? bp->lists + bp->list_rows * prot::kBatchListCap
+                  : nullptr;
     a.phase_bound = bp->phase_bound;
     a.rtime = c->rtime;
     a.err = bp->err;
@@ -1348,7 +1357,7 @@ int prot_solve_cost_rect(prot_ctx *c, const float *C, int64_t n_b, int64_t n_a, 
     const int64_t K = (int64_t)std::floor(1.0 / ei);
     auto enqueue = [&](bool coop) -> int {
         int r = run_loop(c, c->kmat, n_b, n_a, ldk, T, o, 0, mate_a, mate_b, y_a, y_b, K, coop,
-                         OnTheFly(), Copies(), k8);
+                         OnTheFly(), Copies(), k8, 0, true);
         if (r) return r;
         HIP_TRY(c, prot::launch_finalize(n_b, mate_b, c->kmat, ldk, 1, C, ldc, nullptr, nullptr,
                                          0, c->part_k, c->part_c, c->stream, nullptr, 0.0,
@@ -1523,7 +1532,7 @@ int prot_solve_points_rect(prot_ctx *c, const float *X, int64_t n_b, const float
     const int64_t K = (int64_t)std::floor(1.0 / ei);
     auto enqueue = [&](bool coop) -> int {
         int r = run_loop(c, kmat, n_b, n_a, on_the_fly ? round_up(n_a, 8) : ldk, T, o, 0, mate_a,
-                         mate_b, y_a, y_b, K, coop, otf, Copies(), k8);
+                         mate_b, y_a, y_b, K, coop, otf, Copies(), k8, 0, prot::many_dims(d));
         if (r) return r;
         if (on_the_fly)
             HIP_TRY(c, prot::launch_finalize(n_b, mate_b, nullptr, 0, 2, nullptr, 0, X, Y, d,
@@ -1981,7 +1990,7 @@ int prot_batch_create_config(prot_ctx *c, int32_t batch, const int64_t *n_host, 
     }
     if (!rc && batch > 0) rc = setup_teams(c, bp, n_arr, ldk, pt_off, k_off, cfg);
     if (!rc && batch > 0 && bp->team == 0)
-        rc = dev_alloc(c, &bp->lists, (size_t)pts * prot::kBatchListCap);
+        rc = dev_alloc(c, &bp->lists, (size_t)(bp->list_rows = pts) * (prot::kBatchListCap + 1));
     if (rc) {
         prot_batch_destroy(bp);
         return rc;

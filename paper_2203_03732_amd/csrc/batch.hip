@@ -307,6 +307,7 @@ struct LdsJob {
     int64_t T, max_phases, bound;
     int origin;
     int64_t *trace, *rtime;  // may be null
+    const uint32_t *first;   // bounds of lists made beforehand (first_lists_kernel), or null
 };
 // Its totals, and where its free rows are (S.F[cur]).
 struct LdsRun {
@@ -344,11 +345,13 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     const int64_t ldk = J.ldk;
     uint32_t *lists = J.lists;
     const bool timed = J.rtime != nullptr;
-    // no lists (V = 0) and nothing known (minv = 0 makes every row look)
+    // no lists (V = 0) and nothing known (minv = 0 makes every row look), or
+    // the lists made beforehand
     for (int i = tid; i < n; i += NT) {
+        const uint32_t f = J.first && i < J.nb ? J.first[i] : 0u;
         S.key[i] = 0u;
-        S.minv[i] = 0;
-        S.V[i] = 0;
+        S.minv[i] = (uint16_t)f;
+        S.V[i] = (uint16_t)(f >> 16);
     }
     if (tid == 0) {
         S.nF[1] = 0;
@@ -737,7 +740,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
         A.phase_bound ? A.phase_bound
                       : (2 * (int64_t)n * ((int64_t)floor(1.0 / A.eps) + 2) - n) / (T + 1);
     const LdsJob J{n, n, k, ldk, A.lists + off * CAP, T, A.max_phases, bound, A.origin,
-                   nullptr, timed ? A.rtime : nullptr};
+                   nullptr, timed ? A.rtime : nullptr, A.first ? A.first + off : nullptr};
     LdsRun R{};
     lds_cold(J, S);
     lds_phases<NMAX, NT, CAP, false>(J, R, S);
@@ -838,7 +841,7 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     Ctl *c = A.ctl;
     const LdsJob J{A.n_b, A.n_a, A.k, A.ldk, A.lists, A.T, A.max_phases, A.phase_bound, A.origin,
-                   A.trace, nullptr};
+                   A.trace, nullptr, A.cold ? A.first : nullptr};
     const int32_t err = c->err;
     LdsRun R{};
     if (A.cold) {
@@ -906,6 +909,44 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
     }
 }
 
+// The first list of every row of a new instance (t = 0, need = 0), before a
+// solve whose few workgroups would otherwise make them alone: grid (kFirstRows
+// rows a block, instances), a wave its rows one after the other. first[row] =
+// V << 16 | minv. Bound: instruction issue (direct_row), ~2.8 us a row of 2,048
+// and wave; 131,072 such rows take ~0.1 ms, 0.36 on the 64 workgroups of their
+// solve.
+constexpr int kFirstRows = 8;
+template <int NMAX, int CAP, bool kBytes>
+__global__ void __launch_bounds__(256, 4)
+first_lists_kernel(const int32_t *n_arr, const int32_t *ldk_arr, const int64_t *pt_off,
+                   const int64_t *k_off, const int16_t *k_all, int n_b, int n_a, int64_t ldk_one,
+                   uint32_t *lists, uint32_t *first)
+{
+    __shared__ alignas(16) uint16_t zero[NMAX];
+    __shared__ alignas(16) uint32_t stage[4][CAP];
+    const int inst = blockIdx.y;
+    const int nb = n_arr ? n_arr[inst] : n_b, na = n_arr ? nb : n_a;
+    const int64_t ldk = ldk_arr ? ldk_arr[inst] : ldk_one, off = pt_off ? pt_off[inst] : 0;
+    const int16_t *k = k_all + (k_off ? k_off[inst] : 0);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int)blockIdx.x * kFirstRows >= nb) return;
+    for (int i = threadIdx.x; i < NMAX; i += 256) zero[i] = 0;
+    __syncthreads();
+    int window = 4;
+    for (int e = wave; e < kFirstRows; e += 4) {
+        const int b = (int)blockIdx.x * kFirstRows + e;
+        if (b >= nb) return;
+        const RowRegs<NMAX / 512> kr = load_row<NMAX / 512, kBytes>(k, (int64_t)b * ldk, na, lane);
+        uint16_t minv, V;
+        direct_row<NMAX / 512, CAP>(kr, zero, na, 0, 0, lane, stage[wave], &minv, &V, &window);
+        if (V && lane < CAP / 4)
+            *reinterpret_cast<uint4 *>(lists + (off + b) * CAP + lane * 4) =
+                *reinterpret_cast<const uint4 *>(&stage[wave][lane * 4]);
+        if (lane == 0) first[off + b] = ((uint32_t)V << 16) | minv;
+    }
+}
+
 __global__ void batch_reset_kernel(unsigned int *queue) { *queue = 0u; }
 
 // The variant for a batch: n_max picks the LDS layout and the registers a row
@@ -931,6 +972,17 @@ auto with_batch_kernel(int32_t n_max, int32_t batch, F f)
 
 int32_t batch_max_n() { return 2048; }
 
+// The first lists are made beforehand, on every compute unit, where the
+// solve's workgroups leave some idle and rows need lists: in two or three
+// dimensions the first scans mostly find a column among the 512 they look at
+// first. Whole calls in us, without / with: 64 x 2,048, d = 64 5,112 / 4,857;
+// 4 x 2,048, d = 8 1,027 / 608; 8 x 256, d = 32 206 / 194; 256 x 900, d = 16
+// 1,316 / 1,287; but 100 x 2,048, d = 2 1,202 / 1,362 and 50 x 400, d = 3 143 /
+// 155. One instance: a cost matrix of 300 x 517 93 / 82, 300 x 300, d = 16 139 /
+// 114, but 100 x 1,000, d = 8 (nearly every row content at once) 55 / 58.
+bool many_dims(int32_t d) { return d > 3; }
+bool batch_first_lists(int32_t batch, int32_t d) { return batch <= kBatchWideMax && many_dims(d); }
+
 hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     SoloArgs copy = a;
@@ -942,6 +994,22 @@ hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hi
                              : (const void *)solo_kernel<512, 1024, kSoloListCap, kBytes>;
     };
     const void *fn = a.k8 ? pick(std::true_type{}) : pick(std::false_type{});
+    if (a.cold && a.first) {
+        auto lists = [&](auto nmax, auto bytes) {
+            hipLaunchKernelGGL((first_lists_kernel<decltype(nmax)::value, kSoloListCap,
+                                                   decltype(bytes)::value>),
+                               dim3((a.n_b + kFirstRows - 1) / kFirstRows), dim3(256), 0, s,
+                               nullptr, nullptr, nullptr, nullptr, a.k, a.n_b, a.n_a, a.ldk,
+                               a.lists, a.first);
+        };
+        auto by_size = [&](auto bytes) {
+            if (a.n_a > 1024) lists(std::integral_constant<int, 2048>{}, bytes);
+            else if (a.n_a > 512) lists(std::integral_constant<int, 1024>{}, bytes);
+            else lists(std::integral_constant<int, 512>{}, bytes);
+        };
+        if (a.k8) by_size(std::true_type{});
+        else by_size(std::false_type{});
+    }
     return hipExtLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s, ev_start, ev_stop, 0);
 }
 
@@ -965,6 +1033,17 @@ hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipSt
 {
     hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, s, a.queue);
     if (a.batch == 0) return hipGetLastError();
+    if (a.first) {
+        auto lists = [&](auto nmax) {
+            hipLaunchKernelGGL((first_lists_kernel<decltype(nmax)::value, kBatchListCap, false>),
+                               dim3((n_max + kFirstRows - 1) / kFirstRows, a.batch), dim3(256), 0,
+                               s, a.n_arr, a.ldk_arr, a.pt_off, a.k_off, a.k, 0, 0, (int64_t)0,
+                               a.lists, a.first);
+        };
+        if (n_max > 1024) lists(std::integral_constant<int, 2048>{});
+        else if (n_max > 512) lists(std::integral_constant<int, 1024>{});
+        else lists(std::integral_constant<int, 512>{});
+    }
     with_batch_kernel(n_max, a.batch, [&](auto fn, int threads) {
         hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, s, a);
         return 0;

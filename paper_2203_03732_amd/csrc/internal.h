@@ -159,6 +159,7 @@ struct BatchArgs {
     InstanceStats *stats;
     unsigned int *queue;
     uint32_t *lists;          // kBatchListCap entries per row (packed rows): candidate lists
+    uint32_t *first;          // per row: bounds of a list made before the solve (null: none are)
     int64_t phase_bound;      // watchdog: 0 the safe bound, > 0 that many phases, < 0 none
     int64_t *rtime;           // optional diagnostics: 4 int64 per round of the first job
     int32_t *err;             // bit 8: an instance was stopped by the phase-bound watchdog
@@ -235,11 +236,15 @@ struct SoloArgs {
     int32_t k8;               // 1: k is a uint8 matrix
     int64_t max_phases, phase_bound;  // as in LoopArgs
     uint32_t *lists;          // kSoloListCap entries per row
+    uint32_t *first;          // as in BatchArgs, one entry per row
     Ctl *ctl;
     int64_t *trace;
     int32_t *mate_a, *mate_b, *y_a, *y_b;
 };
 hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop);
+// Whether the rows' first lists are made by a kernel of their own.
+bool many_dims(int32_t d);
+bool batch_first_lists(int32_t batch, int32_t d);
 hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipStream_t s);
 
 // loss.hip
