@@ -32,9 +32,10 @@
 // phase of list rows alone takes ~2 us (filter, scan and check, each ended by
 // a workgroup barrier), one with whole rows ~3 us more. Whole batched calls,
 // against keys compared per column and every scan reading the matrix: 512
-// instances of n in [64, 1024], d = 16, eps = 0.05 1.63 -> 1.12 ms; loss and
-// gradient of 64 x 2048, d = 64, eps = 0.01 10.8 -> 5.6 ms (there against
-// teams of 4 workgroups an instance).
+// instances of n in [64, 1024], d = 16, eps = 0.05 1.63 -> 1.12 ms (0.91 with
+// the present cost build); loss and gradient of 64 x 2048, d = 64, eps = 0.01
+// 10.8 -> 5.6 ms (there against teams of 4 workgroups an instance; 5.0 with the
+// present build and first lists).
 #include "cost_common.h"
 #include "device_common.h"
 #include "internal.h"
