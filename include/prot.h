@@ -120,7 +120,9 @@ typedef struct {
     double cost_scale;         /* points: the maximum squared distance m (c = d2/m); cost input: 1 */
     double eps_internal;       /* eps the loop ran with (eps or eps/3) */
     double ms_build;           /* device time of the cost build (0 if none) */
-    double ms_loop_kernel;     /* device time of the persistent phase-loop kernel */
+    double ms_loop_kernel;     /* device time of the phases: the persistent loop, the
+                                  one-workgroup solver of small instances (with its
+                                  completion), or from the one's start to the other's end */
     double ms_total;           /* device time from the first kernel to the last */
 } prot_stats;
 
