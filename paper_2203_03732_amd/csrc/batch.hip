@@ -39,6 +39,7 @@
 #include "cost_common.h"
 #include "device_common.h"
 #include "internal.h"
+#include "round_slots.h"
 
 #include <type_traits>
 
@@ -85,7 +86,9 @@ struct BatchShared {
     long long red_k[16];
     double red_c[16];
     unsigned long long red_s[16];
-    uint32_t nF[2], nl[2], nd[2], prop[2];
+    uint32_t nF[2];
+    // rows with a list, rows without, whether any row proposed: by round_slots.h
+    uint32_t nl[kRoundSlots], nd[kRoundSlots], prop[kRoundSlots];
     uint32_t tr_scan[2], tr_none[2];  // per-phase record: entries examined, rows that found none
     int32_t job;
 };
@@ -356,7 +359,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     }
     if (tid == 0) {
         S.nF[1] = 0;
-        S.nl[0] = S.nl[1] = S.nd[0] = S.nd[1] = S.prop[0] = S.prop[1] = 0;
+        for (int i = 0; i < kRoundSlots; ++i) S.nl[i] = S.nd[i] = S.prop[i] = 0;
         S.tr_scan[0] = S.tr_scan[1] = S.tr_none[0] = S.tr_none[1] = 0;
     }
     int64_t phases = R.phases, sum_free = 0, rounds = 0, max_rounds = R.max_rounds;
@@ -381,6 +384,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     };
     uint32_t r = 0;
     int cur = 0, q = 0;
+    int s = 0;           // slot of the round's counters (round_slots.h)
     int status = R.status;
     int window = 4;      // of this wave's last list (direct_row)
     bool quick = true;   // this wave looks at 512 columns before a whole row
@@ -420,8 +424,8 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
             }
             const uint32_t f = wave_push(&S.nF[nx], skip);
             if (kTrace) none += (uint32_t)__popcll(__ballot(skip));
-            const uint32_t l = wave_push(&S.nl[q], listed);
-            const uint32_t dd = wave_push(&S.nd[q], in && !skip && !listed);
+            const uint32_t l = wave_push(&S.nl[s], listed);
+            const uint32_t dd = wave_push(&S.nd[s], in && !skip && !listed);
             if (skip) {
                 S.y[b] = (uint16_t)(need + 2);
                 S.F[nx][f] = (uint16_t)b;
@@ -437,12 +441,13 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
         int64_t phase_rounds = 0;
         for (;;) {
             r += 1;
-            const uint32_t nl = S.nl[q], nd = S.nd[q];
+            const uint32_t nl = S.nl[s], nd = S.nd[s];
             const int64_t t_start = timed ? (int64_t)wall_clock64() : 0;
             if (tid == 0) {
-                // read by everyone before the last barrier, next used after
-                // the coming one
-                S.nl[q ^ 1] = S.nd[q ^ 1] = S.prop[q ^ 1] = 0;
+                // (nF[cur]: read by everyone before the barrier that began
+                // the phase, next used after the phase)
+                for (int i = 0; i < kRoundSlots; ++i)
+                    if (cleared_by(s, i)) S.nl[i] = S.nd[i] = S.prop[i] = 0;
                 S.nF[cur] = 0;
             }
             // Rows without a list: one wave each, up to 64 of the wave's rows at
@@ -496,7 +501,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                         scanned += (unsigned long long)(j - (int)S.ap[q][at] + 1);
                         S.pa[at] = (uint16_t)a;
                         S.ap[q][at] = (uint16_t)j;
-                        S.prop[q] = 1;
+                        S.prop[s] = 1;
                         atomicMax(&S.key[a], batch_key(r, b));
                     }
                     quick = 2 * __builtin_popcountll(left) <= rows;
@@ -540,7 +545,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                     if (h.j >= 0) {
                         scanned += (unsigned long long)(h.j - pos + 1);
                         S.ap[q][at] = (uint16_t)h.j;
-                        S.prop[q] = 1;
+                        S.prop[s] = 1;
                         atomicMax(&S.key[h.a], batch_key(r, b));
                     } else {
                         scanned += (unsigned long long)(n - pos);
@@ -581,7 +586,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                     scanned += (unsigned long long)((int)j - pos + 1);
                     S.pa[i] = (uint16_t)a;
                     S.ap[q][i] = (uint16_t)j;
-                    S.prop[q] = 1;
+                    S.prop[s] = 1;
                     atomicMax(&S.key[a], batch_key(r, b));
                 } else {
                     scanned += (unsigned long long)(n - pos);
@@ -597,7 +602,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                 J.rtime[4 * (r - 1) + 2] = nl + nd;
                 J.rtime[4 * (r - 1) + 3] = phases;
             }
-            if (S.prop[q]) phase_rounds += 1;
+            if (S.prop[s]) phase_rounds += 1;
             // Winners: step (II), the column's old mate is free in the next
             // phase, and (III a) for the column, y(a) -= 1, at once: every
             // slack v - need is >= 0, so raising t also takes the column out of
@@ -633,8 +638,8 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                 }
                 if (kTrace) none += (uint32_t)__popcll(__ballot(i < top && a == kNone16));
                 const uint32_t f = wave_push(&S.nF[nx], freed != kNone16);
-                const uint32_t l = wave_push(&S.nl[q ^ 1], listed);
-                const uint32_t dd = wave_push(&S.nd[q ^ 1], lost && !listed);
+                const uint32_t l = wave_push(&S.nl[losers_slot(s)], listed);
+                const uint32_t dd = wave_push(&S.nd[losers_slot(s)], lost && !listed);
                 if (freed != kNone16) S.F[nx][f] = (uint16_t)freed;
                 if (lost) {
                     const uint32_t to = listed ? l : (uint32_t)(NMAX - 1) - dd;
@@ -644,7 +649,12 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
             }
             __syncthreads();
             q ^= 1;
-            if (S.nl[q] + S.nd[q] == 0u) break;  // nobody lost a proposal: M' is maximal
+            const int lost_s = losers_slot(s);
+            if (S.nl[lost_s] + S.nd[lost_s] == 0u) {  // nobody lost: M' is maximal
+                s = phase_slot(s);
+                break;
+            }
+            s = lost_s;
         }
         rounds += phase_rounds;
         if (phase_rounds > max_rounds) max_rounds = phase_rounds;
