@@ -844,6 +844,10 @@ __global__ void __launch_bounds__(256) points_wide_kernel(PointsJob j)
                                       : 0.0f;
         const float delta = classify_margin(K);
         const float *th = j.th + (int64_t)blockIdx.z * j.kcap;
+        // A fraction is a number where the sum is one and inv is finite. It is
+        // not at the smallest scales (m eps < 2.9e-39), nor has every sum a
+        // value in a build that met a coordinate that is not finite.
+        const bool fractions = inv <= FLT_MAX && (*j.err & 1) == 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int64_t row = b0 + r8 + i;
@@ -863,9 +867,8 @@ __global__ void __launch_bounds__(256) points_wide_kernel(PointsJob j)
                     g[c] = (int)v;
                 }
                 // (a guess that is far enough from every integer stays what it
-                // is; a NaN's fraction would not show in the maximum, but then
-                // the build is in error)
-                if (!(off <= 0.5f - delta - 1.2e-7f))
+                // is; the maximum does not show a NaN)
+                if (!fractions || !(off <= 0.5f - delta - 1.2e-7f))
 #pragma unroll
                     for (int c = 0; c < 8; ++c) g[c] = refine_k(acc[i][c], g[c], K, th);
             }

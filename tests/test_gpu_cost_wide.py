@@ -81,3 +81,23 @@ def test_non_finite(ctx):
         with pytest.raises(prot.ProtError):
             ctx.solve_points(torch.from_numpy(X).cuda(), torch.zeros_like(torch.from_numpy(X)).cuda(),
                              0.1)
+
+
+@pytest.mark.parametrize("scale", [1e-19, 1e-20, 3e-22])
+@pytest.mark.parametrize("d", [4, 8, 16])
+def test_smallest_scales(ctx, d, scale):
+    """Squared distances down to the smallest binary32 numbers: 1 / (m eps)
+    leaves the range of binary32."""
+    rng = np.random.default_rng(d)
+    X, Y = (rng.random((2500, d), dtype=np.float32) * np.float32(scale) for _ in range(2))
+    k_ref, m_ref = oracle.round_points_f32(X, Y, 0.01)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    k, m = ctx.build_costs(Xd, Yd, 0.01)
+    assert float(m[0]) == m_ref
+    assert np.array_equal(k.cpu().numpy()[:, :2500], k_ref)
+    # a byte matrix is read through the solve
+    res = ctx.solve_points(Xd, Yd, 0.01, k_type="uint8", max_phases=2)
+    ref = oracle.solve_rounded(k_ref, oracle.threshold(0.01, 2500), max_phases=2)
+    assert res.stats["scanned"] == ref["stats"]["scanned"]
+    for name in ("mate_b", "y_a", "y_b"):
+        assert np.array_equal(getattr(res, name).cpu().numpy(), ref[name]), name
