@@ -70,6 +70,9 @@ constexpr int64_t kBarrierTicks = 1000000000ll;
 constexpr int32_t kDualMax = 0x7FFF;           // t (-y(a)) fits its 15-bit field
 // Proposals are combined within a workgroup from this many rows still looking.
 constexpr uint32_t kCombineMin = 16;
+// A slot of the combining table names its column in 18 bits; with more columns
+// every proposal goes to its key directly.
+constexpr int kCombineColumnBits = 18;
 constexpr uint32_t kPublishMin = 256;   // workgroups from which barrier sums are published
 constexpr uint32_t kCombineSlots = 64;  // (768 bytes of LDS)
 constexpr int kGateSpin = 256;                 // gate polls (~0.3 ms) before it closes early
@@ -999,7 +1002,7 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                     // Which waves scan a row does not change what they find.
                     const uint32_t nact = __builtin_amdgcn_readfirstlane(s_nact[r & 1]);
                     if (threadIdx.x == 0) s_nact[(r + 1) & 1] = 0;
-                    combine = R == 1 && nact >= kCombineMin;
+                    combine = R == 1 && nact >= kCombineMin && na <= 1 << kCombineColumnBits;
                     if (kRegroup && nact > 0u && 2u * (uint32_t)R * nact <= (uint32_t)wpg) {
                         const bool mine_row = R == 1 ? ((active >> lane) & 1ull) != 0ull
                                                      : (k_rank == 0 && lane == 0 && (active & 1ull));
@@ -1183,12 +1186,12 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
             bool send = proposed;
             if (combine) {
                 const uint32_t slot = (uint32_t)s_a % kCombineSlots;
-                const uint32_t mine = (r << 18) | ((uint32_t)s_a & 0x3FFFFu);
+                const uint32_t mine = (r << kCombineColumnBits) | (uint32_t)s_a;
                 bool held = false;
                 if (send) {
                     const uint32_t cur = s_ccol[slot];
                     uint32_t owner = cur;
-                    if ((cur ^ mine) >> 18) {
+                    if ((cur ^ mine) >> kCombineColumnBits) {
                         owner = atomicCAS(&s_ccol[slot], cur, mine);
                         if (owner == cur) owner = mine;
                     }
