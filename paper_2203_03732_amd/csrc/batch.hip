@@ -48,6 +48,11 @@ namespace {
 
 constexpr uint32_t kListFill = 0x7FFF0000u;  // column 0 with a k that never matches
 constexpr uint16_t kNone16 = 0xFFFF;
+// Largest y(b) and -y(a): Lemma 3.2 keeps them within K + 2 <= 0x7FFF, so only
+// a cost matrix with entries outside [0, 1] (which its rounding reports) gets
+// one past it; the point builds place every cost in [0, K]. Up to here need
+// stays below the padding's 0x7FFF.
+constexpr uint32_t kDualTop = 0x7FFF;
 constexpr int32_t kBatchWideMax = 256;
 constexpr int32_t kBatchNarrowMaxN = 256, kBatchNarrowMin = 1024;
 // A column's key: the round above the proposing row in reverse order, so that
@@ -90,6 +95,7 @@ struct BatchShared {
     // rows with a list, rows without, whether any row proposed: by round_slots.h
     uint32_t nl[kRoundSlots], nd[kRoundSlots], prop[kRoundSlots];
     uint32_t tr_scan[2], tr_none[2];  // per-phase record: entries examined, rows that found none
+    uint32_t over;  // a dual passed kDualTop
     int32_t job;
 };
 
@@ -317,7 +323,7 @@ struct LdsJob {
 struct LdsRun {
     int64_t phases, sum_free, rounds, max_rounds;
     unsigned long long scanned;  // this thread's share
-    int status;                  // 0, 1 stopped at max_phases, 2 by the bound
+    int status;                  // 0, 1 stopped at max_phases, 2 by the bound, 4 by kDualTop
     int cur;
 };
 
@@ -335,8 +341,9 @@ __device__ void lds_cold(const LdsJob &J, BatchShared<NMAX, NT, CAP> &S)
 }
 
 // The phases from the state in S (t, mate, y, F[0] and nF[0], set by any
-// thread) until at most T rows are free. kTrace: record each phase.
-template <int NMAX, int NT, int CAP, bool kTrace, bool kBytes = false>
+// thread) until at most T rows are free. kSingle: a single instance, whose
+// phases are recorded and whose duals are watched (kDualTop).
+template <int NMAX, int NT, int CAP, bool kSingle, bool kBytes = false>
 __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP> &S)
 {
     constexpr int NC = NMAX / 512;
@@ -359,6 +366,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     }
     if (tid == 0) {
         S.nF[1] = 0;
+        S.over = 0;
         for (int i = 0; i < kRoundSlots; ++i) S.nl[i] = S.nd[i] = S.prop[i] = 0;
         S.tr_scan[0] = S.tr_scan[1] = S.tr_none[0] = S.tr_none[1] = 0;
     }
@@ -389,6 +397,14 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     int window = 4;      // of this wave's last list (direct_row)
     bool quick = true;   // this wave looks at 512 columns before a whole row
     uint32_t block = 8;
+    // A dual rises by at most one a phase, so it can be past kDualTop only after
+    // that many of them; from then on each phase of a single instance looks
+    // before it scans. (A batch's costs are in range; its solves took 1% longer
+    // with the test.)
+    auto look_past_top = [&]() {
+        for (int i = tid; i < n; i += NT)
+            if (S.t[i] > kDualTop || (i < J.nb && S.y[i] > kDualTop)) S.over = 1;
+    };
     __syncthreads();
     for (;;) {
         const uint32_t nF = S.nF[cur];
@@ -423,7 +439,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                 listed = !skip && need < (int)S.V[b];
             }
             const uint32_t f = wave_push(&S.nF[nx], skip);
-            if (kTrace) none += (uint32_t)__popcll(__ballot(skip));
+            if (kSingle) none += (uint32_t)__popcll(__ballot(skip));
             const uint32_t l = wave_push(&S.nl[s], listed);
             const uint32_t dd = wave_push(&S.nd[s], in && !skip && !listed);
             if (skip) {
@@ -436,8 +452,14 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                 S.ap[q][at] = 0;
             }
         }
+        if (kSingle && phases >= (int64_t)kDualTop) look_past_top();
         __syncthreads();
-        if (kTrace) write_trace();
+        // (written between the last barrier and this one only)
+        if (kSingle && phases >= (int64_t)kDualTop && S.over) {
+            status = 4;
+            break;
+        }
+        if (kSingle) write_trace();
         int64_t phase_rounds = 0;
         for (;;) {
             r += 1;
@@ -636,7 +658,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                         S.minv[b] = S.pm[at];
                     }
                 }
-                if (kTrace) none += (uint32_t)__popcll(__ballot(i < top && a == kNone16));
+                if (kSingle) none += (uint32_t)__popcll(__ballot(i < top && a == kNone16));
                 const uint32_t f = wave_push(&S.nF[nx], freed != kNone16);
                 const uint32_t l = wave_push(&S.nl[losers_slot(s)], listed);
                 const uint32_t dd = wave_push(&S.nd[losers_slot(s)], lost && !listed);
@@ -659,7 +681,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
         rounds += phase_rounds;
         if (phase_rounds > max_rounds) max_rounds = phase_rounds;
         cur = nx;
-        if (kTrace) {
+        if (kSingle) {
             const uint32_t sc = wave_sum_u32((uint32_t)(scanned - scanned_before));
             if (lane == 0) {
                 if (sc) atomicAdd(&S.tr_scan[(phases - 1) & 1], sc);
@@ -670,7 +692,12 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
             tr_rounds = phase_rounds;
         }
     }
-    if (kTrace) {
+    if (kSingle && phases >= (int64_t)kDualTop) {
+        look_past_top();
+        __syncthreads();
+        if (S.over) status = 4;
+    }
+    if (kSingle) {
         __syncthreads();
         write_trace();
     }
@@ -854,16 +881,19 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
     const LdsJob J{A.n_b, A.n_a, A.k, A.ldk, A.lists, A.T, A.max_phases, A.phase_bound, A.origin,
                    A.trace, nullptr, A.cold ? A.first : nullptr};
     const int32_t err = c->err;
+    // the loop failed: the outputs are marked invalid (every vertex free); the
+    // host reports the error
+    auto no_matching = [&]() {
+        for (int i = tid; i < A.n_b; i += NT) A.mate_b[i] = -1;
+        for (int i = tid; i < A.n_a; i += NT) A.mate_a[i] = -1;
+    };
     LdsRun R{};
     if (A.cold) {
         lds_cold(J, S);
         if (A.trace && tid < 4) A.trace[tid] = 0;
     } else {
         if (err & kErrLoop) {
-            // the loop failed: the outputs are marked invalid (every vertex
-            // free); the host reports the error
-            for (int i = tid; i < A.n_b; i += NT) A.mate_b[i] = -1;
-            for (int i = tid; i < A.n_a; i += NT) A.mate_a[i] = -1;
+            no_matching();
             return;
         }
         if (err & 16) return;  // (nothing ran)
@@ -890,6 +920,11 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
         }
     }
     lds_phases<NMAX, NT, CAP, true, kBytes>(J, R, S);
+    if (R.status == 4) {
+        if (tid == 0) __hip_atomic_fetch_or(&c->err, 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        no_matching();
+        return;
+    }
     // (a solve stopped early keeps its state, without the completion)
     lds_matching(J, R.cur, A.complete && R.status == 0 && err == 0, S);
     const uint32_t nfree = S.nF[R.cur];

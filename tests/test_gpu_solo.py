@@ -97,3 +97,22 @@ def test_enqueued_and_repeated(ctx):
         ref = oracle.solve_points(X.cpu().numpy(), Y.cpu().numpy(), 0.01)
         for name in ("mate_a", "mate_b", "y_a", "y_b"):
             assert np.array_equal(getattr(res, name).cpu().numpy(), ref[name]), (n, name)
+
+
+@pytest.mark.parametrize("k_type", ["int16", "uint8"])
+@pytest.mark.parametrize("n,bad_rows,eps", [(40, 40, 0.1), (450, 100, 0.05)])
+def test_bad_costs_without_watchdog(ctx, monkeypatch, n, bad_rows, eps, k_type):
+    """Rows that hold only costs far above 1 never find a column; with the
+    watchdog off their duals' range ends the loop."""
+    import functools
+    import paper_2203_03732_amd as prot
+    C = costs(n, n, n)
+    C[:bad_rows] = 1e9
+    monkeypatch.setattr(ctx, "_opts", functools.partial(ctx._opts, phase_bound=-1), raising=False)
+    with pytest.raises(prot.ProtError) as e:
+        ctx.solve_cost(torch.from_numpy(C).cuda(), eps, k_type=k_type)
+    assert e.value.code in (-2, -5)  # range, state
+    if bad_rows == n:
+        assert e.value.code == -5
+    monkeypatch.undo()
+    check(ctx, costs(n, n, n), eps, k_type=k_type)
