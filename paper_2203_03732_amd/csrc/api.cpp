@@ -826,6 +826,7 @@ int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
                 const std::vector<int32_t> &ldk, const std::vector<int64_t> &pt_off,
                 const std::vector<int64_t> &k_off, const prot_batch_config *cfg)
 {
+    bp->phase_bound = bp->opts.phase_bound;  // (teams: in each instance's loop arguments)
     int forced = -1;  // -1 automatic, 0 LDS engine, > 0 that team size
     if (cfg && cfg->engine == PROT_BATCH_ENGINE_LDS) forced = 0;
     else if (cfg && cfg->engine == PROT_BATCH_ENGINE_TEAMS) forced = cfg->team > 0 ? cfg->team : -2;
@@ -843,7 +844,6 @@ int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
     // 2048, d = 64, eps = 0.01 6.2 / 3.0; 32 x 2048 7.9 / 4.3; 4 x 2048, d =
     // 8, eps = 0.02 2.1 / 2.0; 300 x 2048, d = 2 35.7 / 15.6).
     if (forced == 0 || (forced == -1 && bp->n_max <= 1024)) return PROT_OK;
-    if (forced == -1) bp->phase_bound = bp->opts.phase_bound;
     if (forced == -1 && ((bp->d > 3 && bp->eps < 0.04) || bp->batch > kTeamsMaxBatch))
         return PROT_OK;
     const int32_t n_pad_max = (int32_t)round_up(bp->n_max, 8);

@@ -4,6 +4,8 @@ its tiles, lists and packed 16-bit sums can go wrong."""
 import numpy as np
 import pytest
 
+import oracle
+
 from test_gpu_batch import check_instances, ctx, pack  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +65,33 @@ def test_large_duals(ctx, eps):  # noqa: F811
     Ys = [(0.5 + rng.random((n, 2))).astype(np.float32) for n in ns]
     out, stats = run(ctx, ns, Xs, Ys, eps)
     check_instances(ns, Xs, Ys, eps, out, stats)
+
+
+@pytest.mark.parametrize("engine", ["auto", "lds", "teams"])
+@pytest.mark.parametrize("n_max", [1024, 1025])
+@pytest.mark.parametrize("d,eps", [(2, 0.02), (8, 0.02)])
+def test_phase_bound(ctx, monkeypatch, n_max, engine, d, eps):  # noqa: F811
+    """The caller's phase bound stops every instance, whichever engine runs."""
+    import functools
+    import paper_2203_03732_amd as prot
+    rng = np.random.default_rng(n_max)
+    ns = [n_max, 300]
+    Xs = [rng.random((n, d), dtype=np.float32) for n in ns]
+    Ys = [(0.5 + rng.random((n, d))).astype(np.float32) for n in ns]
+    monkeypatch.setattr(prot.Context, "_opts",
+                        staticmethod(functools.partial(prot.Context._opts, phase_bound=3)))
+    plan = ctx.batch(ns, d, eps, config={"engine": engine})
+    plan.run(pack(Xs), pack(Ys), check=False)
+    with pytest.raises(prot.ProtError) as e:
+        plan.status()
+    assert e.value.name == "phase_bound"
+    at = 0
+    for n, X, Y, st in zip(ns, Xs, Ys, plan.stats()):
+        k, _ = oracle.round_points_f32(X, Y, eps)
+        ref = oracle.solve_rounded(k, oracle.threshold(eps, n), max_phases=3, complete=False)
+        assert ref["stats"]["phases"] == 3 and st["phases"] == 3 and st["status"] == -4
+        for name in ("mate_a", "mate_b", "y_a", "y_b"):
+            got = getattr(plan, name)[at:at + n].cpu().numpy()
+            assert np.array_equal(got, ref[name]), name
+        at += n
+    plan.close()
