@@ -70,3 +70,30 @@ def test_bytes_and_solve(ctx):
     for name in ("mate_a", "mate_b", "y_a", "y_b"):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
     assert a.stats["sum_k"] == b.stats["sum_k"]
+
+
+def test_without_workspace(monkeypatch):
+    """Where the screening workspace cannot be had, every pair is taken by the
+    definition."""
+    import paper_2203_03732_amd as prot
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(11)
+    X, Y = vectors("sparse", 300, 784, rng), vectors("sparse", 310, 784, rng)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    ref = oracle.round_l1_normalized_f32(X, Y, 0.1)
+    c = prot.Context(0)
+    try:
+        c.set_cost_metric("l1_normalized")
+        c.solve_points(Xd, Yd, 0.005)  # too fine for the screen: all other workspaces
+        monkeypatch.setenv("PROT_ALLOC_LIMIT", "65536")
+        for limited in (True, False):
+            k, _ = c.build_costs(Xd, Yd, 0.1)
+            assert np.array_equal(k.cpu().numpy()[:, :310], ref), limited
+            res = c.solve_points(Xd, Yd, 0.1)
+            want = oracle.solve_rounded(ref, oracle.threshold(0.1, 300))
+            assert np.array_equal(res.mate_b.cpu().numpy(), want["mate_b"]), limited
+            monkeypatch.delenv("PROT_ALLOC_LIMIT", raising=False)
+    finally:
+        torch.cuda.synchronize()
+        c.close()
