@@ -718,7 +718,7 @@ __global__ void __launch_bounds__(256) points_tile_kernel(PointsJob j)
 // instances of n in [64, 1024], d = 16: maximum 324 -> 213 us, rounding 344 -> 252
 // (of it a third from the shift of the column tiles below); 16,384 x 16,384: 230 and 250.
 constexpr int kWide = 128;
-constexpr int64_t kWideMinN = 257, kWideMinTiles = 1536;
+constexpr int64_t kWideMinN = 257;
 
 template <int PASS, bool kVec>
 __global__ void __launch_bounds__(256) points_wide_kernel(PointsJob j)
@@ -909,20 +909,40 @@ __global__ void __launch_bounds__(256) points_tile_overflow_kernel(PointsJob j)
     }
 }
 
+// Small tiles from which the wide ones are taken (one of those takes as long as
+// four small ones in turn, and needs more coordinates staged at once).
+// Builds of one instance, small / wide tiles, in us:
+// squared, d = 16: 2,450 x 2,560 (1,560 tiles) 61 / 59, 5,000^2 (6,241) 136 / 92,
+//   2,048^2 (1,024) 51 / 53; d = 40: 2,560^2 (1,600) 77 / 75; d = 47: 3,100^2
+//   (2,401) 95 / 101, 5,800^2 (8,281) 226 / 201; d = 64: 4,000^2 (3,969) 143 / 137;
+//   d = 96: 2,944^2 (2,116) 128 / 153, 6,500^2 (10,404) 418 / 413;
+// Euclidean (the rounding's search takes longer in wide tiles), d = 16: 2,600^2
+//   (1,681) 70 / 74, 2,944^2 (2,116) 81 / 80; d = 40: 3,100^2 103 / 104, 5,800^2
+//   240 / 198; d = 64: 5,000^2 210 / 225, 6,000^2 (8,836) 280 / 278; d = 96:
+//   6,500^2 443 / 458.
+// Batches, whole calls: 64 x 300, d = 8 (1,600) 106 / 101, 64 x 2,000 1,102 / 722;
+// but 32 x 300 (800) 103 / 111.
+int64_t wide_min_tiles(const PointsJob &j)
+{
+    if (j.metric == 1) return j.d <= 32 ? 2048 : j.d <= 48 ? 4096 : j.d <= 64 ? 8192 : INT64_MAX;
+    return j.d <= 40 ? 1536 : j.d <= 64 ? 4096 : 8192;
+}
+
 void launch_points_tiled(const PointsJob &j, int64_t n_max, int64_t ldk_max, hipStream_t s)
 {
-    const unsigned rows = (unsigned)((n_max + kTile - 1) / kTile);
-    // Wide tiles where there is work for them on every compute unit (one takes
-    // as long as four small ones in turn) and little of it lies past the edge.
-    // Whole calls, small / wide tiles: n = 2,500, d = 8 (1,600 small tiles) 111 /
-    // 98 us, 64 x 300, d = 8 (1,600) 106 / 101, 64 x 2,000 1,102 / 722; but
-    // 32 x 300 (800) 103 / 111, n = 1,100 (324) 93 / 98, 512 x 129 (4,608, half
-    // of a wide tile empty) 159 / 182.
-    if (n_max >= kWideMinN && (int64_t)rows * rows * j.batch >= kWideMinTiles) {
-        const unsigned wide_rows = (unsigned)((n_max + kWide - 1) / kWide);
+    // rows and columns (of a batch: the largest instance's)
+    const int64_t nb = j.n_arr ? n_max : j.n_single;
+    const int64_t na = j.n_arr || !j.na_single ? nb : j.na_single;
+    auto tiles = [](int64_t n, int64_t tile) {
+        return (unsigned)std::max<int64_t>(1, (n + tile - 1) / tile);
+    };
+    // (a batch of instances that leave half of a wide tile empty, 512 x 129:
+    // 159 / 182 us)
+    if ((!j.n_arr || n_max >= kWideMinN) &&
+        (int64_t)tiles(nb, kTile) * tiles(na, kTile) * j.batch >= wide_min_tiles(j)) {
         const bool vec = j.d % 4 == 0 && (((uintptr_t)j.X | (uintptr_t)j.Y) & 15) == 0;
-        const dim3 gm(wide_rows, wide_rows, j.batch);
-        const dim3 gk((unsigned)((ldk_max + kWide - 1) / kWide), wide_rows, j.batch);
+        const dim3 gm(tiles(na, kWide), tiles(nb, kWide), j.batch);
+        const dim3 gk(tiles(ldk_max, kWide), tiles(nb, kWide), j.batch);
         hipLaunchKernelGGL(vec ? (points_wide_kernel<0, true>) : (points_wide_kernel<0, false>),
                            gm, dim3(256), 0, s, j);
         hipLaunchKernelGGL(thresholds_kernel, dim3(threshold_blocks(j.kcap), 1, j.batch),
@@ -931,12 +951,12 @@ void launch_points_tiled(const PointsJob &j, int64_t n_max, int64_t ldk_max, hip
                            gk, dim3(256), 0, s, j);
         return;
     }
-    hipLaunchKernelGGL(points_tile_kernel<0>, dim3(rows, rows, j.batch), dim3(256), 0, s, j);
+    hipLaunchKernelGGL(points_tile_kernel<0>,
+                       dim3(tiles(na, kTile), tiles(nb, kTile), j.batch), dim3(256), 0, s, j);
     hipLaunchKernelGGL(thresholds_kernel, dim3(threshold_blocks(j.kcap), 1, j.batch), dim3(256),
                        0, s, j);
     hipLaunchKernelGGL(points_tile_kernel<1>,
-                       dim3((unsigned)((ldk_max + kTile - 1) / kTile), rows, j.batch), dim3(256),
-                       0, s, j);
+                       dim3(tiles(ldk_max, kTile), tiles(nb, kTile), j.batch), dim3(256), 0, s, j);
 }
 
 template <int D>

@@ -101,3 +101,26 @@ def test_smallest_scales(ctx, d, scale):
     assert res.stats["scanned"] == ref["stats"]["scanned"]
     for name in ("mate_b", "y_a", "y_b"):
         assert np.array_equal(getattr(res, name).cpu().numpy(), ref[name]), name
+
+
+@pytest.mark.parametrize("metric", ["sqeuclidean", "euclidean"])
+@pytest.mark.parametrize("n_b,n_a,d", [
+    (1, 98305, 4), (70, 49025, 16), (70, 49153, 16),  # thin: 1,534 and 1,538 small tiles
+    (2880, 2881, 7), (2896, 2945, 32), (2945, 2945, 33),  # the Euclidean lines
+    (2561, 2560, 40), (2561, 2560, 41), (4097, 4033, 48), (65, 17, 5)])
+def test_rules(ctx, n_b, n_a, d, metric):
+    """Either side of the lines between small and wide tiles, and rectangles
+    whose grid follows both sides."""
+    rng = np.random.default_rng(n_b + d)
+    X, Y = (rng.standard_normal((n, d), dtype=np.float32) for n in (n_b, n_a))
+    round_f32 = oracle.round_points_f32 if metric == "sqeuclidean" else oracle.round_points_euclid_f32
+    k_ref, m_ref = round_f32(X, Y, 0.02)
+    ctx.set_cost_metric(metric)
+    try:
+        k, m = ctx.build_costs(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), 0.02)
+        k = k.cpu().numpy()
+        assert float(m[0]) == m_ref
+        assert np.array_equal(k[:, :n_a], k_ref)
+        assert (k[:, n_a:] == 0x7FFF).all()
+    finally:
+        ctx.set_cost_metric("sqeuclidean")
