@@ -1978,7 +1978,7 @@ int prot_batch_create_config(prot_ctx *c, int32_t batch, const int64_t *n_host, 
         if (!rc) rc = dev_alloc(c, &bp->th, (size_t)batch * bp->kcap);
         if (!rc) rc = dev_alloc(c, &bp->stats_tmp, (size_t)batch);
         if (!rc) {
-            hipError_t e = prot::batch_grid(n_max, batch, &bp->grid);
+            hipError_t e = prot::batch_grid(n_max, batch, bp->d, bp->eps, &bp->grid);
             if (e != hipSuccess) rc = hip_fail(c, e, "batch occupancy");
         }
     }

@@ -41,6 +41,7 @@
 #include "internal.h"
 #include "round_slots.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace prot {
@@ -53,6 +54,12 @@ constexpr uint16_t kNone16 = 0xFFFF;
 // one past it; the point builds place every cost in [0, K]. Up to here need
 // stays below the padding's 0x7FFF.
 constexpr uint32_t kDualTop = 0x7FFF;
+// Rows of a wave from which they are looked at together (kPeek), and instances
+// whose 16 waves can have as many. Whole solves, from 8 rows and n > 128 / from 4
+// and n > 63, us: 1 x 128, d = 2, eps = 0.2 52.1 / 48.1, 64 x 250, eps = 0.1 71.5 / 67.2;
+// from 2 rows 64 x 50, eps = 0.05 5% slower.
+constexpr int kPeekMin = 4;
+constexpr int32_t kPeekMinN = 63;
 constexpr int32_t kBatchWideMax = 256;
 constexpr int32_t kBatchNarrowMaxN = 256, kBatchNarrowMin = 1024;
 // A column's key: the round above the proposing row in reverse order, so that
@@ -106,6 +113,14 @@ __device__ inline void barrier_lds()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// x, opaque to the compiler: what is made of it where this stands is not kept
+// in registers through the loops around.
+__device__ inline int not_hoisted(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Index for this lane's entry of a list with the given counter (every lane
 // of the wave calls; one atomic per wave).
 __device__ inline uint32_t wave_push(uint32_t *counter, bool want)
@@ -134,6 +149,17 @@ __device__ inline uint32_t pairs_above(uint32_t v, uint32_t D, uint32_t one)
 // Bit e set iff element e of four pairs is at most D, from the OR of
 // pairs_above(word w) << 2w.
 __device__ inline uint32_t low_bits(uint32_t x) { return ~(x | (x >> 15)) & 0xFFu; }
+
+// Bit i set iff any of bits 4 i .. 4 i + 3 is.
+__device__ inline uint32_t rows_of(unsigned long long x)
+{
+    x |= x >> 2;
+    x = (x | x >> 1) & 0x1111111111111111ull;
+    x = (x | x >> 3) & 0x0303030303030303ull;
+    x = (x | x >> 6) & 0x000F000F000F000Full;
+    x = (x | x >> 12) & 0x000000FF000000FFull;
+    return (uint32_t)(x | x >> 24) & 0xFFFFu;
+}
 
 // The rounded costs of columns col0 .. col0 + 7 of a row. A matrix of bytes
 // (kBytes) holds padding as 0xFF, which becomes the 0x7FFF of a 16-bit one.
@@ -342,8 +368,9 @@ __device__ void lds_cold(const LdsJob &J, BatchShared<NMAX, NT, CAP> &S)
 
 // The phases from the state in S (t, mate, y, F[0] and nF[0], set by any
 // thread) until at most T rows are free. kSingle: a single instance, whose
-// phases are recorded and whose duals are watched (kDualTop).
-template <int NMAX, int NT, int CAP, bool kSingle, bool kBytes = false>
+// phases are recorded and whose duals are watched (kDualTop). kPeek: rows are
+// likely to find their column at once (rows_content).
+template <int NMAX, int NT, int CAP, bool kSingle, bool kBytes, bool kPeek>
 __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP> &S)
 {
     constexpr int NC = NMAX / 512;
@@ -396,6 +423,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
     int status = R.status;
     int window = 4;      // of this wave's last list (direct_row)
     bool quick = true;   // this wave looks at 512 columns before a whole row
+    bool peek = true;    // and at 32 before those (kPeek)
     uint32_t block = 8;
     // A dual rises by at most one a phase, so it can be past kDualTop only after
     // that many of them; from then on each phase of a single instance looks
@@ -489,6 +517,53 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                         int c = (J.origin == 0 ? b : 0) + pos;
                         return c >= n ? c - n : c;
                     };
+                    // Many rows: first the 32 columns from each row's position,
+                    // 16 rows at a time, 4 lanes a row. On while at least half
+                    // the rows hit.
+                    if (kPeek && peek && rows >= kPeekMin) {
+                        const int ln = not_hoisted(lane);
+                        auto peek_at = [&](int e, int *b, int *c) {
+                            *b = -1;
+                            uint4 kv = make_uint4(~0u, ~0u, ~0u, ~0u);
+                            if (e < rows) {
+                                *b = S.ab[q][slot(e)];
+                                *c = start_of(*b, S.ap[q][slot(e)]);
+                                const int col0 = (*c & ~7) + (ln & 3) * 8;
+                                if (col0 < n) kv = load_8<kBytes>(k, (int64_t)*b * ldk + col0);
+                            }
+                            return kv;
+                        };
+                        int bn, cn = 0;
+                        uint4 kn = peek_at(ln >> 2, &bn, &cn);
+                        for (int e0 = 0; e0 < rows; e0 += 16) {
+                            const int b = bn, c = cn, e = e0 + (ln >> 2);
+                            const uint4 kv = kn;
+                            if (e0 + 16 < rows) kn = peek_at(e + 16, &bn, &cn);
+                            const int origin = J.origin == 0 ? b : 0;
+                            const int end = c < origin ? origin : n;
+                            const int col0 = (c & ~7) + (ln & 3) * 8;
+                            uint32_t m = 0;
+                            if (b >= 0 && col0 < end)
+                                m = match_mask(kv, *reinterpret_cast<const uint4 *>(&S.t[col0]),
+                                               (int)S.y[b] - 1) &
+                                    range_mask(col0, c, end);
+                            // the first of a row's lanes with a hit proposes
+                            const uint32_t lower = (1u << (ln & 3)) - 1u;
+                            const bool mine =
+                                m != 0u && ((uint32_t)(__ballot(m != 0u) >> (ln & 60)) & lower) == 0u;
+                            if (mine) {
+                                const int a = col0 + __builtin_ctz(m), at = slot(e);
+                                const int j = a >= origin ? a - origin : a - origin + n;
+                                scanned += (unsigned long long)(j - (int)S.ap[q][at] + 1);
+                                S.pa[at] = (uint16_t)a;
+                                S.ap[q][at] = (uint16_t)j;
+                                S.prop[s] = 1;
+                                atomicMax(&S.key[a], batch_key(r, b));
+                            }
+                            left &= ~((unsigned long long)rows_of(__ballot(mine)) << e0);
+                        }
+                        peek = 2 * __builtin_popcountll(left) <= rows;
+                    }
                     auto load_window = [&](int e, int *b, int *c) {
                         *b = __builtin_amdgcn_readfirstlane((int)S.ab[q][slot(e)]);
                         *c = start_of(*b, __builtin_amdgcn_readfirstlane((int)S.ap[q][slot(e)]));
@@ -497,11 +572,15 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                                         : make_uint4(~0u, ~0u, ~0u, ~0u);
                     };
                     int bn, cn;
-                    uint4 kn = load_window(0, &bn, &cn);
-                    for (int e = 0; e < rows; ++e) {
+                    uint4 kn;
+                    unsigned long long todo = left;
+                    if (todo) kn = load_window(__builtin_ctzll(todo), &bn, &cn);
+                    while (todo) {
+                        const int e = __builtin_ctzll(todo);
                         const int b = bn, c = cn, at = slot(e);
                         const uint4 kv = kn;
-                        if (e + 1 < rows) kn = load_window(e + 1, &bn, &cn);
+                        todo &= todo - 1ull;
+                        if (todo) kn = load_window(__builtin_ctzll(todo), &bn, &cn);
                         const int need = __builtin_amdgcn_readfirstlane((int)S.y[b] - 1);
                         const int col0 = (c & ~7) + lane * 8;
                         // a scan that started at origin + pos wraps at n and ends
@@ -575,7 +654,7 @@ __device__ void lds_phases(const LdsJob &J, LdsRun &R, BatchShared<NMAX, NT, CAP
                     }
                 }
                 store_list();
-                if (2 * overflowed >= full) quick = true;
+                if (2 * overflowed >= full) quick = peek = true;
             }
             // rows with a list: kListLanes lanes each
             for (uint32_t i0 = wave * (64 / kListLanes); i0 < nl; i0 += NT / kListLanes) {
@@ -762,7 +841,7 @@ __device__ void lds_matching(const LdsJob &J, int cur, bool complete, BatchShare
     __syncthreads();
 }
 
-template <int NMAX, int NT, int CAP>
+template <int NMAX, int NT, int CAP, bool kPeek>
 __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, NT, CAP> &S, bool timed)
 {
     constexpr int kWaves = NT / 64;
@@ -781,7 +860,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
                    nullptr, timed ? A.rtime : nullptr, A.first ? A.first + off : nullptr};
     LdsRun R{};
     lds_cold(J, S);
-    lds_phases<NMAX, NT, CAP, false>(J, R, S);
+    lds_phases<NMAX, NT, CAP, false, false, kPeek>(J, R, S);
     unsigned long long scanned = R.scanned;
     const int status = R.status == 2 ? -4 : R.status;
     if (R.status == 2 && tid == 0)
@@ -846,7 +925,7 @@ __device__ void solve_instance(const BatchArgs &A, int inst, BatchShared<NMAX, N
     __syncthreads();
 }
 
-template <int NMAX, int NT>
+template <int NMAX, int NT, bool kPeek>
 // (4 waves per SIMD: two workgroups of 512 threads or one of 1,024 a CU)
 __global__ void __launch_bounds__(NT, 4) batch_solve_kernel(BatchArgs A)
 {
@@ -859,7 +938,7 @@ __global__ void __launch_bounds__(NT, 4) batch_solve_kernel(BatchArgs A)
         const int job = S.job;
         __syncthreads();
         if (job >= A.batch) break;
-        solve_instance<NMAX, NT, kBatchListCap>(A, A.order[job], S, A.rtime != nullptr && job == 0);
+        solve_instance<NMAX, NT, kBatchListCap, kPeek>(A, A.order[job], S, A.rtime != nullptr && job == 0);
     }
 }
 
@@ -919,7 +998,7 @@ __global__ void __launch_bounds__(NT, 4) solo_kernel(SoloArgs A)
             if (is_free) S.F[0][f] = (uint16_t)i;
         }
     }
-    lds_phases<NMAX, NT, CAP, true, kBytes>(J, R, S);
+    lds_phases<NMAX, NT, CAP, true, kBytes, false>(J, R, S);
     if (R.status == 4) {
         if (tid == 0) __hip_atomic_fetch_or(&c->err, 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         no_matching();
@@ -1001,17 +1080,33 @@ __global__ void batch_reset_kernel(unsigned int *queue) { *queue = 0u; }
 // with layouts of 1,024 -> 512 columns: 10 x 500 407 -> 374, 8 x 256 235 -> 218
 // (16 waves); 512 x [300, 500] 554 -> 508 (8 waves; 16: 593, 4: 608);
 // 2,000 x [100, 256], 8 -> 4 waves 649 -> 585, but 306 x [39, 247] 174 -> 215.
-template <class F>
-auto with_batch_kernel(int32_t n_max, int32_t batch, F f)
+template <bool kPeek, class F>
+auto pick_batch_kernel(int32_t n_max, int32_t batch, F f)
 {
-    if (n_max > 1024) return f(batch_solve_kernel<2048, 1024>, 1024);
+    if (n_max > 1024) return f(batch_solve_kernel<2048, 1024, kPeek>, 1024);
     if (n_max > 512)
-        return batch > kBatchWideMax ? f(batch_solve_kernel<1024, 512>, 512)
-                                     : f(batch_solve_kernel<1024, 1024>, 1024);
-    if (batch <= kBatchWideMax) return f(batch_solve_kernel<512, 1024>, 1024);
+        return batch > kBatchWideMax ? f(batch_solve_kernel<1024, 512, kPeek>, 512)
+                                     : f(batch_solve_kernel<1024, 1024, kPeek>, 1024);
+    if (batch <= kBatchWideMax) return f(batch_solve_kernel<512, 1024, kPeek>, 1024);
     return n_max <= kBatchNarrowMaxN && batch >= kBatchNarrowMin
-               ? f(batch_solve_kernel<512, 256>, 256)
-               : f(batch_solve_kernel<512, 512>, 512);
+               ? f(batch_solve_kernel<512, 256, kPeek>, 256)
+               : f(batch_solve_kernel<512, 512, kPeek>, 512);
+}
+
+// Whether most rows have so many columns at their smallest cost that they find
+// one among the first they look at and are done in a few phases: large eps in
+// few dimensions. A wave then looks at 32 columns of 16 rows at once before it
+// takes rows singly (kPeek): whole solves without / with, us: d = 2 1 x 1,000, eps =
+// 0.2 98 / 61, 64 x 1,024, eps = 0.1 167 / 120; but 512 x [64, 1024], d = 16, eps = 0.05,
+// beyond the line, 915 / 925 (its registers), and 64 x 250, d = 2, eps = 0.01 2,346 /
+// 2,420.
+bool rows_content(int32_t d, double eps) { return eps > 0.0167 * std::pow((double)d, 0.86); }
+
+template <class F>
+auto with_batch_kernel(int32_t n_max, int32_t batch, int32_t d, double eps, F f)
+{
+    return n_max > kPeekMinN && rows_content(d, eps) ? pick_batch_kernel<true>(n_max, batch, f)
+                                                     : pick_batch_kernel<false>(n_max, batch, f);
 }
 
 }  // namespace
@@ -1059,10 +1154,10 @@ hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hi
     return hipExtLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s, ev_start, ev_stop, 0);
 }
 
-hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid)
+hipError_t batch_grid(int32_t n_max, int32_t batch, int32_t d, double eps, int *grid)
 {
     int per_cu = 0, dev = 0, cus = 0;
-    hipError_t e = with_batch_kernel(n_max, batch, [&](auto fn, int threads) {
+    hipError_t e = with_batch_kernel(n_max, batch, d, eps, [&](auto fn, int threads) {
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
     });
     if (e != hipSuccess) return e;
@@ -1090,7 +1185,7 @@ hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipSt
         else if (n_max > 512) lists(std::integral_constant<int, 1024>{});
         else lists(std::integral_constant<int, 512>{});
     }
-    with_batch_kernel(n_max, a.batch, [&](auto fn, int threads) {
+    with_batch_kernel(n_max, a.batch, a.d, a.eps, [&](auto fn, int threads) {
         hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), 0, s, a);
         return 0;
     });

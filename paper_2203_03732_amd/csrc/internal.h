@@ -218,7 +218,7 @@ hipError_t launch_points_mfma(const PointsJob &j, const MfmaAux &x, int64_t n_ma
 // batch.hip
 constexpr int kBatchListCap = 32;
 int32_t batch_max_n();
-hipError_t batch_grid(int32_t n_max, int32_t batch, int *grid);
+hipError_t batch_grid(int32_t n_max, int32_t batch, int32_t d, double eps, int *grid);
 // One instance solved by one workgroup (n_a <= kSoloMaxN), with its completion.
 constexpr int64_t kSoloMaxN = 2048;
 constexpr int64_t kSoloMaxK = 16000;        // 2 K + 2 stays below the padding's 0x7FFF
