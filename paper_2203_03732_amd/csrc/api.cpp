@@ -1004,7 +1004,7 @@ int batch_enqueue(prot_batch *bp, hipStream_t s, const float *X, const float *Y,
     a.stats = reinterpret_cast<prot::InstanceStats *>(stats ? stats : bp->stats_tmp);
     a.queue = bp->queue;
     a.lists = bp->lists;
-    a.first = prot::batch_first_lists(bp->batch, bp->d)
+    a.first = prot::batch_first_lists(bp->batch, bp->d, bp->eps)
                   ? bp->lists + bp->list_rows * prot::kBatchListCap
                   : nullptr;
     a.phase_bound = bp->phase_bound;

@@ -1095,11 +1095,14 @@ auto pick_batch_kernel(int32_t n_max, int32_t batch, F f)
 
 // Whether most rows have so many columns at their smallest cost that they find
 // one among the first they look at and are done in a few phases: large eps in
-// few dimensions. A wave then looks at 32 columns of 16 rows at once before it
-// takes rows singly (kPeek): whole solves without / with, us: d = 2 1 x 1,000, eps =
-// 0.2 98 / 61, 64 x 1,024, eps = 0.1 167 / 120; but 512 x [64, 1024], d = 16, eps = 0.05,
-// beyond the line, 915 / 925 (its registers), and 64 x 250, d = 2, eps = 0.01 2,346 /
-// 2,420.
+// few dimensions. Then lists made beforehand are wasted: whole solves of 16 x 700
+// without / with them, us: d = 4 eps = 0.1 87 / 96, 0.05 246 / 245; d = 8 0.14 99 / 106,
+// 0.07 262 / 223; d = 16 0.3 96 / 106, 0.14 184 / 132; d = 32 0.3 170 / 152. The line is
+// a fit to where the two meet at d = 4, 5, 8, 16 and 32. And a wave looks at 32
+// columns of 16 rows at once before it takes rows singly (kPeek): without / with,
+// d = 2 1 x 1,000, eps = 0.2 98 / 61, 64 x 1,024, eps = 0.1 167 / 120; but 512 x [64, 1024],
+// d = 16, eps = 0.05, beyond the line, 915 / 925 (its registers), and 64 x 250, d = 2,
+// eps = 0.01 2,346 / 2,420.
 bool rows_content(int32_t d, double eps) { return eps > 0.0167 * std::pow((double)d, 0.86); }
 
 template <class F>
@@ -1122,7 +1125,10 @@ int32_t batch_max_n() { return 2048; }
 // 155. One instance: a cost matrix of 300 x 517 93 / 82, 300 x 300, d = 16 139 /
 // 114, but 100 x 1,000, d = 8 (nearly every row content at once) 55 / 58.
 bool many_dims(int32_t d) { return d > 3; }
-bool batch_first_lists(int32_t batch, int32_t d) { return batch <= kBatchWideMax && many_dims(d); }
+bool batch_first_lists(int32_t batch, int32_t d, double eps)
+{
+    return batch <= kBatchWideMax && many_dims(d) && !rows_content(d, eps);
+}
 
 hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop)
 {

@@ -244,7 +244,7 @@ struct SoloArgs {
 hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop);
 // Whether the rows' first lists are made by a kernel of their own.
 bool many_dims(int32_t d);
-bool batch_first_lists(int32_t batch, int32_t d);
+bool batch_first_lists(int32_t batch, int32_t d, double eps);
 hipError_t launch_batch_solve(const BatchArgs &a, int32_t n_max, int grid, hipStream_t s);
 
 // loss.hip
