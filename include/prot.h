@@ -378,8 +378,10 @@ int prot_batch_create(prot_ctx *ctx, int32_t batch, const int64_t *n_host, int32
  *            with its state in LDS (n <= 2048) and short lists of candidate
  *            columns per row in memory; PROT_BATCH_ENGINE_TEAMS: `team`
  *            workgroups of the persistent phase loop per instance;
- *            PROT_BATCH_ENGINE_AUTO: LDS, except teams for at most 32
- *            instances of n_max > 1024 with d <= 3 or (internal) eps >= 0.04.
+ *            PROT_BATCH_ENGINE_AUTO: LDS, except teams for at most 64
+ *            instances of n_max > 1024 at middle values of (internal) eps,
+ *            where rows have more columns at their smallest costs than a
+ *            list holds.
  *   team     TEAMS: workgroups per instance, 1..8 (0: as many as fit);
  *            PROT_E_UNSUPPORTED if fewer than ceil(n_max / 1024) or more
  *            than fit next to each other on the GPU.

@@ -825,11 +825,35 @@ int upload(prot_ctx *c, T **dst, const std::vector<T> &src)
     return PROT_OK;
 }
 
+// The automatic choice for instances above 1,024 points (below, always one
+// workgroup). Teams win where a row has more columns at its smallest costs than
+// a candidate list holds, yet not so many that it finds one at once and is done
+// in a few phases: between two lines in eps that rise with d; below the lower
+// one the lists pay, and the more so the smaller the instance. With more than 32
+// instances a team has fewer workgroups than it could use, so teams have to be
+// ahead by more. Whole solves, teams / one workgroup, in ms: lower line, n =
+// 2,000, 16 instances: d = 2 eps 0.01 10.4 / 10.1, 0.02 4.3 / 4.8; d = 5 0.02 3.5 /
+// 3.2, 0.035 1.7 / 2.2; d = 8 0.03 2.0 / 1.9, 0.045 1.2 / 1.5; d = 64 0.03 1.3 times as
+// fast with one, 0.1 0.89 times; n = 1,100: d = 4 0.03 1.6 / 1.5, 0.045 0.95 / 1.03.
+// Upper line, n = 2,000: d = 3 0.1 0.36 / 0.46, 0.16 1.13 times as fast with one; d = 5
+// 0.12 0.75 times, 0.18 1.05 times. By batch, d = 5, eps = 0.05, n = 2,000: 48
+// instances 1.5 / 1.8, 64 1.7 / 2.0, 100 2.4 / 2.1; d = 2 48 1.37 / 1.44, 64 1.59 / 1.53;
+// d = 3, eps = 0.035 64 0.91 / 1.00.
+bool teams_pay(int32_t n_max, int32_t batch, int32_t d, double eps)
+{
+    if (n_max <= 1024) return false;
+    const double lo = std::min(0.0075 * std::pow((double)d, 0.7), 0.055) *
+                      std::max(1.0, 1.0 + (1800 - n_max) / 1000.0);
+    const double hi = 0.08 + 0.015 * d;
+    if (batch <= 32) return eps >= lo && eps < hi;  // 256 CUs / teams of 8
+    return batch <= (d > 2 ? 64 : n_max > 1536 ? 48 : 32) && eps >= 1.3 * lo &&
+           eps < (d > 3 ? 0.8 : 0.95) * hi;
+}
+
 // Chooses between the LDS-resident batched kernel (one workgroup per
-// instance) and teams of phase-loop workgroups, and for teams builds every
-// instance's loop arguments and workspace. PROT_BATCH_TEAM=<w> forces w
+// instance) and teams of phase-loop workgroups (teams_pay), and for teams builds
+// every instance's loop arguments and workspace. PROT_BATCH_TEAM=<w> forces w
 // workgroups per instance (0: never use teams).
-constexpr int32_t kTeamsMaxBatch = 32;  // 256 CUs / teams of 8
 int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
                 const std::vector<int32_t> &ldk, const std::vector<int64_t> &pt_off,
                 const std::vector<int64_t> &k_off, const prot_batch_config *cfg)
@@ -840,19 +864,7 @@ int setup_teams(prot_ctx *c, prot_batch *bp, const std::vector<int32_t> &n_arr,
     else if (cfg && cfg->engine == PROT_BATCH_ENGINE_TEAMS) forced = cfg->team > 0 ? cfg->team : -2;
     else if (const char *v = std::getenv("PROT_BATCH_TEAM")) forced = std::atoi(v);
     const bool must = cfg && cfg->engine == PROT_BATCH_ENGINE_TEAMS;
-    // Automatic choice: one workgroup per instance, except for few large
-    // instances (each can have 8 workgroups) where the candidate lists do not
-    // pay: in two or three dimensions a row has more admissible columns than
-    // a list holds and every scan reads the matrix (n = 2048, d = 2: eps =
-    // 0.05 0.19 ms by teams, 0.25 by one workgroup; 8 instances, eps = 0.01,
-    // shifted clouds 14.1 against 14.8 ms), and at large eps a solve has too
-    // few phases to earn back the first lists (n = 1100, d = 16, eps = 0.1, 2
-    // phases: 0.17 against 0.37 ms; n = 1200, d = 4, eps = 0.05: 0.13 against
-    // 0.16). Elsewhere one workgroup wins (ms, teams / one workgroup: 1 x
-    // 2048, d = 64, eps = 0.01 6.2 / 3.0; 32 x 2048 7.9 / 4.3; 4 x 2048, d =
-    // 8, eps = 0.02 2.1 / 2.0; 300 x 2048, d = 2 35.7 / 15.6).
-    if (forced == 0 || (forced == -1 && bp->n_max <= 1024)) return PROT_OK;
-    if (forced == -1 && ((bp->d > 3 && bp->eps < 0.04) || bp->batch > kTeamsMaxBatch))
+    if (forced == 0 || (forced == -1 && !teams_pay(bp->n_max, bp->batch, bp->d, bp->eps)))
         return PROT_OK;
     const int32_t n_pad_max = (int32_t)round_up(bp->n_max, 8);
     int gm = 0;

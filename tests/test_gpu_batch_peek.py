@@ -1,7 +1,8 @@
 """Batches whose rows find their column among the first they look at (large eps,
 few dimensions): 16 rows of a wave looked at together, 32 columns each. Every
 instance bit-exact with the CPU oracle at the sizes where the groups of rows and
-the windows end, in every kernel width."""
+the windows end, in every kernel width, and on both sides of the choice between
+one workgroup and teams."""
 import numpy as np
 import pytest
 
@@ -44,4 +45,18 @@ def test_widths(ctx, batch, n_max):  # noqa: F811
     plan.run(pack(Xs), pack(Ys))
     check_instances(ns, Xs, Ys, 0.15, (plan.mate_a, plan.mate_b, plan.y_a, plan.y_b), plan.stats(),
                     which=list(range(0, batch, 7)) + [batch - 1])
+    plan.close()
+
+
+@pytest.mark.parametrize("batch,n,d,eps", [
+    (3, 1100, 2, 0.02), (3, 1100, 2, 0.04), (2, 1600, 3, 0.05), (2, 1600, 3, 0.14),
+    (34, 1100, 5, 0.1), (50, 1100, 2, 0.1), (66, 1040, 6, 0.1)])
+def test_teams_or_one(ctx, batch, n, d, eps):  # noqa: F811
+    """Either side of the automatic choice above 1,024 points."""
+    ns = [n] * batch
+    Xs, Ys = sets(ns, d, "uniform", n)
+    plan = ctx.batch(ns, d, eps)
+    plan.run(pack(Xs), pack(Ys))
+    check_instances(ns, Xs, Ys, eps, (plan.mate_a, plan.mate_b, plan.y_a, plan.y_b), plan.stats(),
+                    which=[0, batch - 1])
     plan.close()
