@@ -73,6 +73,11 @@ constexpr uint32_t kCombineMin = 16;
 // A slot of the combining table names its column in 18 bits; with more columns
 // every proposal goes to its key directly.
 constexpr int kCombineColumnBits = 18;
+// Copies of a transport: from this many workgroups (~1,500 copies). Fewer never
+// queue long at a column, and counting the rows that look costs each round
+// (loop, counted / not: 467 copies 666 / 652 us, 760 867 / 851, 1,169 696 / 684;
+// 1,550, 97 workgroups, 392 / 395 without it).
+constexpr uint32_t kCombineCopiesMin = 94;
 constexpr uint32_t kPublishMin = 256;   // workgroups from which barrier sums are published
 constexpr uint32_t kCombineSlots = 64;  // (768 bytes of LDS)
 constexpr int kGateSpin = 256;                 // gate polls (~0.3 ms) before it closes early
@@ -792,7 +797,10 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
     // way; the n = 10,000 Euclidean loop 10.2 -> 9.8 ms by publishing).
     const bool publish = !kMulti && nwg >= kPublishMin;
     const uint32_t xcd = kMulti ? 0u : xcd_id();
-    const int grp = (int)(kMulti ? wg % (uint32_t)G
+    // The copies of a transport leave few rows looking in a round, and the words
+    // are better spread by index while they are polled (2,300 copies 4,089 / 4,010
+    // us, 3,901 1,883 / 1,838; plain loops of 2,100 to 3,000 rows are 1 to 2% slower so).
+    const int grp = (int)(kMulti || (kCopies && !publish) ? wg % (uint32_t)G
                                  : (xcd + kXcds * (wg % (uint32_t)((G + kXcds - 1) / kXcds))) %
                                        (uint32_t)G);
     if (publish) {
@@ -993,11 +1001,12 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
                 // lost finds the next copy of the same column right after it,
                 // so its scans stay short and teams only add overhead)
                 constexpr bool kRegroup = !kCopies;
+                const bool counted = kRegroup || nwg >= kCombineCopiesMin;
                 const bool counts = R == 1 ? (active != 0ull) : (k_rank == 0 && (active & 1ull));
-                if (R < 16 && lane == 0 && counts)
+                if (counted && R < 16 && lane == 0 && counts)
                     atomicAdd(&s_nact[r & 1], R == 1 ? (uint32_t)__popcll(active) : 1u);
                 __syncthreads();
-                if (R < 16) {
+                if (counted && R < 16) {
                     // Once the workgroup's rows still looking fit in half its
                     // waves per team (or, in slot mode, in half its waves),
                     // the phase continues with teams twice as large or more
