@@ -1149,9 +1149,10 @@ hipError_t launch_solo(const SoloArgs &a, hipStream_t s, hipEvent_t ev_start, hi
                                nullptr, nullptr, nullptr, nullptr, a.k, a.n_b, a.n_a, a.ldk,
                                a.lists, a.first);
         };
+        // (kSoloColdCells entries and n_a <= 2 n_b: at most 565 columns)
+        static_assert(2 * kSoloColdCells <= 1024 * 1024, "columns of a solve from the start");
         auto by_size = [&](auto bytes) {
-            if (a.n_a > 1024) lists(std::integral_constant<int, 2048>{}, bytes);
-            else if (a.n_a > 512) lists(std::integral_constant<int, 1024>{}, bytes);
+            if (a.n_a > 512) lists(std::integral_constant<int, 1024>{}, bytes);
             else lists(std::integral_constant<int, 512>{}, bytes);
         };
         if (a.k8) by_size(std::true_type{});

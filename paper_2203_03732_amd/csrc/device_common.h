@@ -115,15 +115,15 @@ __device__ inline uint32_t wave_min_u32(uint32_t v)
     v = min(v, dpp_u32<kDppBcast31, 0xC>(0xFFFFFFFFu, v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
-// minimum over each group of N = 8, 16 or 32 lanes, in all of them
+// minimum over each group of N = 8 or 16 lanes, in all of them
 template <int N>
 __device__ inline uint32_t group_min_u32(uint32_t v)
 {
+    static_assert(N == 8 || N == 16, "lanes of a group");
     v = min(v, dpp_u32<kDppXor1>(0xFFFFFFFFu, v));
     v = min(v, dpp_u32<kDppXor2>(0xFFFFFFFFu, v));
     v = min(v, dpp_u32<kDppHalfMirror>(0xFFFFFFFFu, v));
     if constexpr (N >= 16) v = min(v, dpp_u32<kDppMirror>(0xFFFFFFFFu, v));
-    if constexpr (N >= 32) v = min(v, (uint32_t)__shfl_xor((int)v, 16));
     return v;
 }
 
