@@ -216,13 +216,15 @@ __device__ inline void put_k(T *k, int64_t at, int g)
 
 // 64 G x 64 G pairs per block, 4 G x 4 G per thread (rows and columns in G
 // groups of 4, so that 16 lanes read 256 consecutive bytes of a staged word),
-// kSadWords words staged per step in two buffers, the next step's words in
-// registers meanwhile. v_sad_u16 adds two |x - y| to a 32-bit sum. G = 2, and
-// G = 1 where that leaves too few blocks for the chip (launch_l1_pairs).
-// Bound: vector issue, with G = 2 64 instructions per word and thread against
-// 4 LDS reads. 10,000 x 10,000 pairs of 784 pixels, 529 of them used: 0.95 ms
-// (the issue of these instructions alone takes 0.71), against 3.09 ms by the
-// definition for all pairs.
+// kSadWords words staged per step in two buffers. v_sad_u16 adds two |x - y| to a
+// 32-bit sum. G = 2, and G = 1 where that leaves too few blocks for the chip
+// (launch_l1_pairs). With G = 1 the next step's words wait in registers while this
+// one's are added; with G = 2 the compiler keeps those 16 words in scratch (80
+// bytes a lane): a step's loads are waited for, and stored there, before its sums.
+// Bound: with G = 2 64 vector instructions per word and thread against 4 LDS reads,
+// and those loads. 10,000 x 10,000 pairs of 784 pixels, 529 of them used: 0.95 ms,
+// of which the issue of the instructions takes 0.71; 3.09 ms by the definition for
+// all pairs.
 template <class T, int G>
 __global__ void __launch_bounds__(256) l1_sad_kernel(PointsJob j)
 {

@@ -56,8 +56,11 @@ constexpr int kPrefetch = 6;        // chunks in flight in a long scan
 constexpr int kSlotBatch = 4;       // rows whose first chunks are loaded together
 constexpr int kTeamPrefetch = 4;    // chunks in flight per wave of a team scan
 
-// Round words: workgroup w adds to word w % G of the round; each word sums
-// over the workgroups of its group that arrived.
+// Round words: a workgroup adds to its group's word of the round; each word sums
+// over the workgroups of its group that arrived. The group is the XCD a workgroup
+// runs on, so groups differ in size and between launches (with published sums
+// everyone registers first and reads its group's size); batched teams, and
+// transport copies on less than kPublishMin workgroups, group by index, w % G.
 constexpr int kShiftFree = 21, kShiftLose = 42, kShiftArrive = 53;
 constexpr unsigned long long kField = (1ull << 21) - 1;
 constexpr uint16_t kTaken = 0x8000;            // mark: column taken earlier in the phase
@@ -793,8 +796,10 @@ phase_loop_kernel(LoopArgs A0, const LoopArgs *__restrict__ arr, int team, int32
     // instead of ~0.6; but the sum is seen ~0.3 us later, so that few
     // workgroups, which arrive together, poll the words (solves of
     // ~1,000 and 2,104 rows, 63 and 132 workgroups: 3% faster so, of 4,000, 250
-    // workgroups, 2%; 4,200 and 5,000 rows, 256 workgroups: the same either
-    // way; the n = 10,000 Euclidean loop 10.2 -> 9.8 ms by publishing).
+    // workgroups, 2%). Loop times from 256 workgroups on, polled / published:
+    // Euclidean, 4,200 rows 1.270 / 1.239 ms, 5,000 8.30 / 7.84, 10,000 11.68 / 11.31;
+    // squared, 10,000 0.288 / 0.282, 50,000 0.882 / 0.880. (Against groups by index
+    // and no combining the same loops took 1.257, 8.31, 11.53, 0.287 and 0.899.)
     const bool publish = !kMulti && nwg >= kPublishMin;
     const uint32_t xcd = kMulti ? 0u : xcd_id();
     // The copies of a transport leave few rows looking in a round, and the words
