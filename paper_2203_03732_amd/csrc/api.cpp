@@ -526,17 +526,21 @@ int next_loop_events(prot_ctx *c, hipEvent_t **out)
     return PROT_OK;
 }
 
+// What is known of the costs when the one-workgroup solver is considered.
+struct CostHints {
+    bool first_lists = false;  // rows have few columns at their smallest costs
+    bool many_phases = false;  // the Euclidean cost: the small costs take many values
+};
+
 // The phase loop on n rows (B) and n_a >= n columns (A), with its init and
 // finish kernels. K: the largest rounded cost (for the watchdog and the
 // warm-start check). cooperative: launch the loop cooperatively (the retry after the gate
-// admitted too few workgroups). first_lists: rows are expected to have few
-// columns at their smallest costs (the one-workgroup solver's lists are made
-// beforehand).
+// admitted too few workgroups).
 int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk, int64_t T,
              const prot_opts *o, int32_t warm, int32_t *mate_a, int32_t *mate_b, int32_t *y_a,
              int32_t *y_b, int64_t K, bool cooperative = false,
              const OnTheFly &otf = OnTheFly(), const Copies &cp = Copies(), int k8 = 0,
-             int64_t trace_off = 0, bool first_lists = false)
+             int64_t trace_off = 0, const CostHints &hints = CostHints())
 {
     int rc = ensure_loop(c, n_a);
     if (rc) return rc;
@@ -619,13 +623,21 @@ int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk,
     //   512 x 512, 64 dimensions 169 -> 198.
     // - Else it takes over once at most kSoloFewRows rows are free, if a good
     //   part of the phases is still to come then: their number grows with
-    //   free / T, the change costs 10 to 15 us (n = 1,024: T = 51 313 -> 262 us,
-    //   T = 102, d = 64 175 -> 183), a whole row of more than 1,024 columns
-    //   twice as long (n = 2,048: T = 20 474 -> 383 us, T = 102 196 -> 222), and
-    //   rows that have spare columns are soon done (512 x 1,500: 5 phases, 123 -> 156).
+    //   free / T, the change costs 3 to 10 us (n = 1,024: T = 51 313 -> 262 us,
+    //   T = 102, d = 64 175 -> 183), and rows that have spare columns are soon
+    //   done (512 x 1,500: 5 phases, 123 -> 156). Above 1,024 columns a whole row
+    //   takes twice as long. Euclidean costs have phases enough (n = 2,000, T = 32
+    //   1.33 times as fast, 1,800 x 2,000, T = 28 1.08 times); squared ones of points
+    //   up to T ~ 20 (n = 2,000, T = 20 1.11 times, T = 32 1.02; 1,900 x 2,000, T = 9 1.38
+    //   times, T = 19 0.98) and given matrices up to T ~ 12 (uniform costs, n = 2,000,
+    //   T = 10 1.18 times, T = 20 1.0, T = 32 0.91; 1,800 x 2,000, T = 9 0.95).
     const bool solo_cold = n * n_a <= prot::kSoloColdCells;
-    const bool solo_tail = n_a <= 1024 ? 2 * T <= prot::kSoloFewRows
-                                       : 4 * T <= prot::kSoloFewRows && 8 * (n_a - n) <= n_a;
+    const int64_t spare = n_a - n;
+    const bool solo_tail =
+        n_a <= 1024         ? 2 * T <= prot::kSoloFewRows
+        : hints.many_phases ? 4 * T <= prot::kSoloFewRows && 8 * spare <= n_a
+                            : (spare == 0 && !hints.first_lists ? 6 : 10) * T <= prot::kSoloFewRows &&
+                                  16 * spare <= n_a;
     const bool solo = n_a <= prot::kSoloMaxN && K <= prot::kSoloMaxK && !warm && !otf.d &&
                       !cp.rmap && !cooperative && !c->loop_knobs && !c->rtime &&
                       (solo_cold || solo_tail);
@@ -643,7 +655,7 @@ int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk,
         so.max_phases = a.max_phases;
         so.phase_bound = a.phase_bound;
         so.lists = c->solo_lists;
-        so.first = first_lists && n_a <= 2 * n
+        so.first = hints.first_lists && n_a <= 2 * n
                        ? c->solo_lists + prot::kSoloMaxN * prot::kSoloListCap
                        : nullptr;
         so.ctl = c->ctl;
@@ -1377,7 +1389,7 @@ int prot_solve_cost_rect(prot_ctx *c, const float *C, int64_t n_b, int64_t n_a, 
     const int64_t K = (int64_t)std::floor(1.0 / ei);
     auto enqueue = [&](bool coop) -> int {
         int r = run_loop(c, c->kmat, n_b, n_a, ldk, T, o, 0, mate_a, mate_b, y_a, y_b, K, coop,
-                         OnTheFly(), Copies(), k8, 0, true);
+                         OnTheFly(), Copies(), k8, 0, CostHints{true, false});
         if (r) return r;
         HIP_TRY(c, prot::launch_finalize(n_b, mate_b, c->kmat, ldk, 1, C, ldc, nullptr, nullptr,
                                          0, c->part_k, c->part_c, c->stream, nullptr, 0.0,
@@ -1552,7 +1564,8 @@ int prot_solve_points_rect(prot_ctx *c, const float *X, int64_t n_b, const float
     const int64_t K = (int64_t)std::floor(1.0 / ei);
     auto enqueue = [&](bool coop) -> int {
         int r = run_loop(c, kmat, n_b, n_a, on_the_fly ? round_up(n_a, 8) : ldk, T, o, 0, mate_a,
-                         mate_b, y_a, y_b, K, coop, otf, Copies(), k8, 0, prot::many_dims(d));
+                         mate_b, y_a, y_b, K, coop, otf, Copies(), k8, 0,
+                         CostHints{prot::many_dims(d), c->cost_metric == PROT_METRIC_EUCLIDEAN});
         if (r) return r;
         if (on_the_fly)
             HIP_TRY(c, prot::launch_finalize(n_b, mate_b, nullptr, 0, 2, nullptr, 0, X, Y, d,

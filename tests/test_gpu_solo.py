@@ -116,3 +116,32 @@ def test_bad_costs_without_watchdog(ctx, monkeypatch, n, bad_rows, eps, k_type):
         assert e.value.code == -5
     monkeypatch.undo()
     check(ctx, costs(n, n, n), eps, k_type=k_type)
+
+
+@pytest.mark.parametrize("kind,n_b,n_a,eps", [
+    ("cost", 2048, 2048, 0.006), ("cost", 2048, 2048, 0.0063), ("cost", 1900, 2000, 0.0065),
+    ("cost", 1874, 2000, 0.006),                                     # too many spare columns
+    ("points", 2041, 2041, 0.0103), ("points", 2041, 2041, 0.011), ("points", 2040, 2048, 0.005),
+    ("euclidean", 1793, 2048, 0.0175), ("euclidean", 1791, 2048, 0.0175)])
+def test_rule_above_1024(ctx, kind, n_b, n_a, eps):
+    """Either side of the lines between the grid's loop alone and the hand-over
+    to one workgroup, above 1,024 columns."""
+    if kind == "cost":
+        C = costs(n_b, n_a, n_b, low=True)
+        check(ctx, C, eps, max_phases=60)
+        return
+    rng = np.random.default_rng(n_b)
+    X, Y = (rng.random((n, 2), dtype=np.float32) for n in (n_b, n_a))
+    ctx.set_cost_metric("sqeuclidean" if kind == "points" else kind)
+    try:
+        res = ctx.solve_points(*(torch.from_numpy(a).cuda() for a in (X, Y)), eps)
+    finally:
+        ctx.set_cost_metric("sqeuclidean")
+    round_f32 = oracle.round_points_f32 if kind == "points" else oracle.round_points_euclid_f32
+    k, _ = round_f32(X, Y, eps)
+    ref = oracle.solve_rounded(k, oracle.threshold(eps, n_b), trace=True)
+    for name in ("mate_a", "mate_b", "y_a", "y_b"):
+        assert np.array_equal(getattr(res, name).cpu().numpy(), ref[name]), name
+    for s in ("phases", "rounds", "max_rounds", "scanned", "sum_free", "sum_k"):
+        assert res.stats[s] == ref["stats"][s], s
+    assert np.array_equal(ctx.trace(), ref["trace"])
