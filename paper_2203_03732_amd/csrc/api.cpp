@@ -200,6 +200,9 @@ int64_t phase_bound_for(const prot_opts *o, int64_t n_b, int64_t n_a, int64_t K,
 // enqueues the loop again with a cooperative launch.
 constexpr int kRetryCooperative = 1000;
 
+// (Re)allocates *p; on failure it is null. The callers that grow several arrays
+// together set their capacity to 0 first, so that a failure in between leaves no
+// capacity that some array does not have.
 template <class T>
 int dev_alloc(prot_ctx *c, T **p, size_t count)
 {
@@ -227,6 +230,7 @@ int ensure_loop(prot_ctx *c, int64_t n)
     if (n <= c->cap_n && c->key) return PROT_OK;
     const int64_t cap = n < 1024 ? 1024 : n;
     int rc;
+    c->cap_n = 0;
     if ((rc = dev_alloc(c, &c->key, (size_t)cap))) return rc;
     if ((rc = dev_alloc(c, &c->t, (size_t)round_up(cap, 8)))) return rc;
     if ((rc = dev_alloc(c, &c->lists, (size_t)cap * 2))) return rc;
@@ -559,6 +563,7 @@ int run_loop(prot_ctx *c, const int16_t *k, int64_t n, int64_t n_a, int64_t ldk,
     if (tg) {
         const int64_t need = (int64_t)grid * round_up(n_a, 8);
         if (need > c->tpriv_cap) {
+            c->tpriv_cap = 0;
             if ((rc = dev_alloc(c, &c->tpriv, (size_t)need))) return rc;
             c->tpriv_cap = need;
         }
@@ -1612,6 +1617,7 @@ int ensure_ot(prot_ctx *c, int64_t n_b, int64_t n_a, int64_t cb, int64_t ca)
     int rc = PROT_OK;
     if (!w.info && (rc = dev_alloc(c, &w.info, 1))) return rc;
     if (n_b > w.cap_b) {
+        w.cap_b = 0;
         if ((rc = dev_alloc(c, &w.s_off, (size_t)n_b + 1)) ||
             (rc = dev_alloc(c, &w.ymax, (size_t)n_b)) || (rc = dev_alloc(c, &w.rv, (size_t)n_b)) ||
             (rc = dev_alloc(c, &w.R, (size_t)n_b + 1)))
@@ -1619,22 +1625,26 @@ int ensure_ot(prot_ctx *c, int64_t n_b, int64_t n_a, int64_t cb, int64_t ca)
         w.cap_b = n_b;
     }
     if (n_a > w.cap_a) {
+        w.cap_a = 0;
         if ((rc = dev_alloc(c, &w.d_off, (size_t)n_a + 1)) ||
             (rc = dev_alloc(c, &w.qv, (size_t)n_a)) || (rc = dev_alloc(c, &w.Q, (size_t)n_a + 1)))
             return rc;
         w.cap_a = n_a;
     }
     if (n_b * n_a > w.cap_cells) {
+        w.cap_cells = 0;
         if ((rc = dev_alloc(c, &w.cnt, (size_t)(n_b * n_a)))) return rc;
         w.cap_cells = n_b * n_a;
     }
     if (cb > w.cap_cb) {
+        w.cap_cb = 0;
         if ((rc = dev_alloc(c, &w.row_pt, (size_t)cb)) || (rc = dev_alloc(c, &w.mate_b, (size_t)cb)) ||
             (rc = dev_alloc(c, &w.y_b, (size_t)cb)))
             return rc;
         w.cap_cb = cb;
     }
     if (ca > w.cap_ca) {
+        w.cap_ca = 0;
         if ((rc = dev_alloc(c, &w.col_pt, (size_t)ca)) || (rc = dev_alloc(c, &w.mate_a, (size_t)ca)) ||
             (rc = dev_alloc(c, &w.y_a, (size_t)ca)))
             return rc;
@@ -1765,6 +1775,7 @@ int ensure_clusters(prot_ctx *c, int64_t n_b, int64_t n_a)
     prot_ctx::Ot &w = c->ot;
     int rc = PROT_OK;
     if (n_b > w.ccap_b) {
+        w.ccap_b = 0;
         if ((rc = dev_alloc(c, &w.cY, (size_t)n_b)) || (rc = dev_alloc(c, &w.cF, (size_t)n_b)) ||
             (rc = dev_alloc(c, &w.cPF, (size_t)n_b + 1)) ||
             (rc = dev_alloc(c, &w.cact, (size_t)n_b)) ||
@@ -1773,6 +1784,7 @@ int ensure_clusters(prot_ctx *c, int64_t n_b, int64_t n_a)
         w.ccap_b = n_b;
     }
     if (n_a > w.ccap_a) {
+        w.ccap_a = 0;
         if ((rc = dev_alloc(c, &w.cZ, (size_t)n_a)) || (rc = dev_alloc(c, &w.ctop, (size_t)n_a)) ||
             (rc = dev_alloc(c, &w.cbot, (size_t)n_a)) || (rc = dev_alloc(c, &w.cG, (size_t)n_a)) ||
             (rc = dev_alloc(c, &w.cmsum, (size_t)n_a)) ||
@@ -1782,17 +1794,20 @@ int ensure_clusters(prot_ctx *c, int64_t n_b, int64_t n_a)
         w.ccap_a = n_a;
     }
     if (n_b * n_a > w.ccap_cells) {
+        w.ccap_cells = 0;
         if ((rc = dev_alloc(c, &w.cw, (size_t)(n_b * n_a)))) return rc;
         w.ccap_cells = n_b * n_a;
     }
     const int64_t staged = n_b * round_up(n_a, 4) + 8;
     if (staged > w.ccap_stage) {
+        w.ccap_stage = 0;
         if ((rc = dev_alloc(c, &w.cstage, (size_t)staged))) return rc;
         w.ccap_stage = staged;
     }
     if (!w.csync && (rc = dev_alloc(c, &w.csync, (size_t)prot::kSyncWords))) return rc;
     const int64_t words = n_a * ((n_b + 63) / 64);
     if (words > w.ccap_mask) {
+        w.ccap_mask = 0;
         if ((rc = dev_alloc(c, &w.cmask, (size_t)words))) return rc;
         w.ccap_mask = words;
     }
